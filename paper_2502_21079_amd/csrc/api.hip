@@ -77,7 +77,7 @@ adaspa_status check_select(const adaspa_problem* p, const adaspa_select* s) {
 }
 
 struct WsLayout {
-  size_t idx, prefix, curve, headk, base, claim, total;
+  size_t sums, headk, base, claim, total;
 };
 
 WsLayout workspace_layout(const adaspa_problem* p) {
@@ -86,11 +86,14 @@ WsLayout workspace_layout(const adaspa_problem* p) {
   const size_t rows = bh * nb;
   WsLayout w;
   size_t off = 0;
-  w.idx = off;    off = align_up(off + rows * nb * sizeof(int32_t));
-  w.prefix = off; off = align_up(off + rows * nb * sizeof(int64_t));
-  w.curve = off;  off = align_up(off + bh * nb * sizeof(int64_t));
+  // A few sums per row or a partial curve per group of rows, and no less than
+  // the 12 bytes per mass that callers' buffers are sized for.
+  const size_t per_wg = (size_t)select_rows_per_wg((int)rows);
+  const size_t parts = bh * ((nb + per_wg - 1) / per_wg) * nb;
+  const size_t sums = (parts > 4 * rows ? parts : 4 * rows) * sizeof(int64_t);
+  w.sums = off;   off = align_up(off + (sums > 12 * rows * nb ? sums : 12 * rows * nb));
   w.headk = off;  off = align_up(off + bh * sizeof(int32_t));
-  w.base = off;   off = align_up(off + bh * sizeof(int64_t));
+  w.base = off;   off = align_up(off + bh * sizeof(int32_t));
   w.claim = off;  off = align_up(off + 9 * sizeof(uint32_t));   // mass-pass work queues (cleared as nine)
   w.total = off;
   return w;
@@ -192,11 +195,9 @@ adaspa_status enqueue_selection(const adaspa_problem* prob, const adaspa_select*
   P.col_idx = col_idx;
   P.head_k_out = head_k;
   P.head_recall_out = head_recall;
-  P.ws_idx = (int32_t*)(ws + wl.idx);
-  P.ws_prefix = (int64_t*)(ws + wl.prefix);
-  P.ws_curve = (int64_t*)(ws + wl.curve);
+  P.ws_sums = (int64_t*)(ws + wl.sums);
   P.ws_headk = (int32_t*)(ws + wl.headk);
-  P.ws_base = (int64_t*)(ws + wl.base);
+  P.ws_base = (int32_t*)(ws + wl.base);
   P.batch_heads = bh;
   P.heads = prob->heads;
   P.nb = nb;

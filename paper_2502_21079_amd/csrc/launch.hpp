@@ -57,6 +57,15 @@ struct MassParams {
 constexpr int kMaxHeads = 512;
 constexpr int kMaxBlocks = 8192;
 
+// Rows whose masses one workgroup of the coverage curve adds up (four waves,
+// each one to sixteen rows): few enough for four workgroups per CU, and at
+// most 64, so that the partial curves each head's workgroup then adds up stay
+// few.
+inline int select_rows_per_wg(int rows) {
+  const int per_wave = rows / 4096;
+  return 4 * (per_wave < 1 ? 1 : (per_wave > 16 ? 16 : per_wave));
+}
+
 struct SelectParams {
   const float* w;             // [R, nb] masses, R = B*H*nb rows
   int32_t* row_ptr;
@@ -64,11 +73,12 @@ struct SelectParams {
   int32_t* head_k_out;        // may be null
   float* head_recall_out;     // may be null
   // workspace
-  int32_t* ws_idx;            // [R, nb] key-block order per row
-  int64_t* ws_prefix;         // [R, nb] cumulative Q32 mass in that order
-  int64_t* ws_curve;          // [B*H, nb] kept(k) for k = 1..nb
+  int64_t* ws_sums;           // exact sums between the kernels: two per row (TOPK), partial curves
+                              // [B*H, n_parts, nb] (COVERAGE), [B*H, n_parts, 4] (HIERARCHICAL)
   int32_t* ws_headk;          // [B*H]
-  int64_t* ws_base;           // [B*H] first col_idx entry of each head
+  int32_t* ws_base;           // [B*H] first col_idx entry of each head (many heads only)
+  int rows_per_wg, n_parts;   // COVERAGE: rows of one partial curve; parts per head (also HIERARCHICAL)
+  int base_ready;             // ws_base holds the heads' first entries (both set by the launcher)
   int batch_heads;
   int heads;
   int nb;
@@ -92,6 +102,6 @@ hipError_t launch_fused_search(AttnParams a, MassParams m, int head_dim, hipStre
 // Q K^T (a.ylog, a.ylse2: scratch of B*H*nkb*L and B*H*L floats; a.wmass:
 // the masses), then the masses summed from the scratch.
 hipError_t launch_single_pass_search(AttnParams a, int head_dim, hipStream_t st);
-hipError_t launch_select(const SelectParams& p, hipStream_t st);
+hipError_t launch_select(SelectParams p, hipStream_t st);
 
 }  // namespace adaspa
