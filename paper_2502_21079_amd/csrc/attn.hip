@@ -990,15 +990,15 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_sparse_pair_ker
 constexpr int kMassRing = 128;        // blocks of W per row held in LDS before they are written out
 
 // The mass pass of query-block group pg of head bh (QB query blocks, 256
-// rows).  qsrc(qf, nlse2, hoff, qrow, qvalid, hw) supplies this lane's Q
+// rows) over the key blocks [kb0, kb1).  qsrc(qf, nlse2, hoff, qrow, qvalid, hw) supplies this lane's Q
 // fragments and -LSE * log2(e) of its row (-inf for a row past L, whose
 // exp2 terms are then 0); sK0 / sK1 are the two K tile buffers, sRed the
 // per-wave sums of the last two blocks and sW the ring of W blocks not yet
 // written out.
 template <int D, int QB, int NW, typename QSrc>
-__device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int pg, QSrc&& qsrc,
-                                                u16* sK0, u16* sK1, float (*sRed)[NW],
-                                                float (*sW)[kMassRing]) {
+__device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int pg, int kb0, int kb1,
+                                                QSrc&& qsrc, u16* sK0, u16* sK1,
+                                                float (*sRed)[NW], float (*sW)[kMassRing]) {
   constexpr int NT = 64 * NW;
   constexpr int WPB = NW / QB;       // waves per query block
   constexpr int SUB = 32 * WPB / KT; // KT-key tiles per key block
@@ -1023,7 +1023,9 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
   qsrc(qf, nlse2, hoff, qrow, qvalid, hw);
   const float sl2 = a.scale_log2;
   const int sub = SUB;
-  const int nfull = L / KT;   // full key tiles
+  const bool to_end = kb1 == a.nkb;
+  const int t0 = kb0 * SUB;                             // the range's full key tiles [t0, nfull)
+  const int nfull = to_end ? L / KT : kb1 * SUB;
   float* wrow = a.w + ((size_t)bh * a.nkb + p0) * a.nkb;    // row p0 + qb at wrow + qb * nkb
   const int nrows = a.nkb - p0 < QB ? a.nkb - p0 : QB;      // rows of W this group owns
 
@@ -1040,10 +1042,10 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
   // adone and is reduced over the wave in the middle of step t + 1, under
   // its MFMAs, so the end of step t does not wait for that chain; it is
   // published after step t + 1's barrier.  bdone is its block, -1 when none
-  // waits; npub counts the blocks published so far.
+  // waits; blocks [kb0, npub) are published.
   float adone = 0.f;
   int bdone = -1;
-  int npub = 0;
+  int npub = kb0;
   // After a barrier: waves combined in a fixed order (deterministic).
   auto publish = [&](int blk) {
     if (tid == 0) {
@@ -1059,8 +1061,8 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
   // After a barrier that follows the publication of block blk: once a chunk
   // of CHUNK blocks is complete, write it out (it is not touched again until
   // the ring wraps, CHUNK blocks and at least one barrier later).
-  int flushed = 0;                  // blocks [0, flushed) written out
-  auto flush = [&](int done) {      // blocks [0, done) published
+  int flushed = kb0;                // blocks [kb0, flushed) written out
+  auto flush = [&](int done) {      // blocks [kb0, done) published
     while (done - flushed >= CHUNK) {
       if (tid < CHUNK * QB) {
         const int qb = tid / CHUNK, i = flushed + tid % CHUNK;
@@ -1071,20 +1073,20 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
   };
   __syncthreads();
 
-  if (nfull > 0) {
-    KDMA::issue(rK, sK0, 0, wave, lane);
-    if (nfull > 1) KDMA::issue(rK, sK1, KT, wave, lane);
+  if (nfull > t0) {
+    KDMA::issue(rK, sK0, t0 * KT, wave, lane);
+    if (nfull > t0 + 1) KDMA::issue(rK, sK1, (t0 + 1) * KT, wave, lane);
     wait_vmem();
     __syncthreads();
     f32x16 s_cur[2];
     qk_tile<D, KS>(sK0, qf, c32, hw, s_cur);
-    __syncthreads();            // sK0 is refilled by step 0
+    __syncthreads();            // sK0 is refilled by the first step
 
     KLoader<D, NW> ld;
     ld.init(wave, lane);
     const int klane = (c32 * KS + hw) * 8;
     // Step t (t + 1 < nfull) sums tile t, forms the scores of tile t+1 from
-    // buffer (t+1)&1 and loads tile t+2 into buffer t&1.
+    // one buffer and loads tile t+2 into the other.
     // Past the last tile the load is clamped to the last one (an in-range
     // load into a buffer that is not read again), so no load is branched.
     auto step = [&](int t, const u16* rdK, u16* ldK) {
@@ -1124,7 +1126,7 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
         npub = reduced + 1;
       }
     };
-    int t = 0;
+    int t = t0;
     for (; t + 2 < nfull; t += 2) {
       step(t, sK1, sK0);
       step(t + 1, sK0, sK1);
@@ -1150,7 +1152,7 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
     }
   }
   // Ragged last tile (L not a multiple of KT), with key masking.
-  if (nfull * KT < L) {
+  if (to_end && nfull * KT < L) {
     __syncthreads();
     KDMA::issue(rK, sK0, nfull * KT, wave, lane);
     wait_vmem();
@@ -1162,14 +1164,14 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
     for (int e = 0; e < 32; ++e) acc += fast_exp2(fmaf(s[e >> 4][e & 15], sl2, nlse2));
   }
   // The last block, when its tiles did not end on a block boundary.
-  if (nfull % sub != 0 || nfull * KT < L) {
+  if (to_end && (nfull % sub != 0 || nfull * KT < L)) {
     finish_block(a.nkb - 1);
     __syncthreads();
     publish(a.nkb - 1);
   }
   __syncthreads();
   for (int qb = 0; qb < nrows; ++qb)
-    for (int i = flushed + tid; i < a.nkb; i += NT) wrow[(size_t)qb * a.nkb + i] = sW[qb][i % RING];
+    for (int i = flushed + tid; i < kb1; i += NT) wrow[(size_t)qb * a.nkb + i] = sW[qb][i % RING];
 }
 
 template <int D, int QB, int NW>
@@ -1182,8 +1184,10 @@ __global__ __launch_bounds__(64 * NW, 2) void block_mass_kernel(MassParams a) {
 
   const int ngrp = (a.nkb + QB - 1) / QB;    // query-block groups per head
   // One contiguous range of (head, query-block group) items per XCD, through
-  // the per-XCD work queues when a workspace is given (see claim_item).
-  int bh, pg;
+  // the per-XCD work queues when a workspace is given (see claim_item).  The
+  // first n_whole items walk all key blocks; the others are dealt out in
+  // n_split ranges of key blocks each (plan_mass_items).
+  int bh, pg, kb0 = 0, kb1 = a.nkb;
   {
     int item = (int)blockIdx.x;
     if (a.claim != nullptr) {
@@ -1193,7 +1197,16 @@ __global__ __launch_bounds__(64 * NW, 2) void block_mass_kernel(MassParams a) {
       item = s_item;
       if (item < 0) return;
     }
-    const int lid = xcd_remap(item, a.n_items);
+    int lid;
+    if (item < a.n_whole) {
+      lid = xcd_remap(item, a.n_whole);
+    } else {
+      const int sub = xcd_remap(item - a.n_whole, a.n_items - a.n_whole);
+      const int part = sub % a.n_split;
+      lid = a.n_whole + sub / a.n_split;
+      kb0 = (int)((int64_t)a.nkb * part / a.n_split);
+      kb1 = (int)((int64_t)a.nkb * (part + 1) / a.n_split);
+    }
     bh = lid / ngrp;
     pg = lid % ngrp;
   }
@@ -1202,7 +1215,7 @@ __global__ __launch_bounds__(64 * NW, 2) void block_mass_kernel(MassParams a) {
     // A padding row (past L) gets -inf: exp2 of it is 0 and it adds nothing.
     nlse2 = qvalid ? -a.lse[(size_t)bh * a.seqlen + qrow] * kLog2e : -INFINITY;
   };
-  block_mass_body<D, QB, NW>(a, bh, pg, qsrc, sK0, sK1, sRed, sW);
+  block_mass_body<D, QB, NW>(a, bh, pg, kb0, kb1, qsrc, sK0, sK1, sRed, sW);
 }
 
 // ---------------------------------------------------------------------------
@@ -1234,7 +1247,7 @@ __global__ __launch_bounds__(512, 1) void fused_search_kernel(AttnParams a, Mass
       for (int i = 0; i < D / 16; ++i) q2[i] = qf[i];
       nlse2 = qvalid ? -lse * kLog2e : -INFINITY;
     };
-    block_mass_body<D, QB, NW>(m, bh, qt, qsrc, ring, ring + LD::ELEMS,
+    block_mass_body<D, QB, NW>(m, bh, qt, 0, m.nkb, qsrc, ring, ring + LD::ELEMS,
                                reinterpret_cast<float (*)[NW]>(sums),
                                reinterpret_cast<float (*)[kMassRing]>(sums + 2 * NW));
   });
@@ -1382,10 +1395,36 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   return launch_attn<128, 4, true>(a, st);
 }
 
+// Work items of the mass pass.  512 workgroups run at a time (two per CU), so
+// n items of equal cost take ceil(n / 512) rounds: whole rounds of items walk
+// all their key blocks, and the items of the last, partial round are split
+// into as many ranges of key blocks as make it shortest (a key block's masses
+// do not depend on the others, so a split changes no result).  A range costs
+// its tiles and about kMassRangeTiles more for its Q and first tiles.
+constexpr int kMassSlots = 512;
+constexpr int kMassRangeTiles = 6;
+static void plan_mass_items(MassParams& a, int n) {
+  const int tiles = (a.seqlen + KT - 1) / KT;
+  a.n_whole = n / kMassSlots * kMassSlots;
+  const int rest = n - a.n_whole;
+  a.n_split = 1;
+  double best = 1e30;
+  for (int s = 1; s <= a.nkb && s <= 64; ++s) {
+    const double rounds = (double)(((int64_t)rest * s + kMassSlots - 1) / kMassSlots);
+    const double cost = rounds * ((double)tiles / s + kMassRangeTiles);
+    if (cost < best * 0.999) {
+      best = cost;
+      a.n_split = s;
+    }
+  }
+  a.n_items = a.n_whole + rest * a.n_split;
+}
+
 template <int D, int QB, int NW>
 static hipError_t launch_mass_t(MassParams a, hipStream_t st) {
-  a.n_items = (a.nkb + QB - 1) / QB * a.batch_heads;
+  plan_mass_items(a, (a.nkb + QB - 1) / QB * a.batch_heads);
   a.n_wg = a.n_items;
+  if (a.n_items <= kMassSlots) a.claim = nullptr;    // all run at once: nothing to balance
   if (a.claim != nullptr) {                  // as in launch_dense
     a.n_wg = a.n_items + (a.n_items + 3) / 4;
     hipLaunchKernelGGL(claim_reset_kernel, dim3(1), dim3(64), 0, st, a.claim);

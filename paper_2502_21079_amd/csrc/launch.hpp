@@ -51,7 +51,8 @@ struct MassParams {
   int n_wg;
   float scale_log2;
   uint32_t* claim;            // 8 work-queue counters (one per XCD), or null
-  int n_items;                // with claim: work items (head, query-block group)
+  int n_items;                // work items (set by the launcher): n_whole (head, query-block group)
+  int n_whole, n_split;       // items over all key blocks, then n_split ranges of each other one
 };
 
 constexpr int kMaxHeads = 512;
