@@ -76,6 +76,8 @@ adaspa_status check_select(const adaspa_problem* p, const adaspa_select* s) {
   return ADASPA_OK;
 }
 
+bool key_split(const adaspa_problem* p) { return use_key_split((int64_t)p->batch * p->heads, p->seqlen); }
+
 struct WsLayout {
   size_t sums, headk, base, claim, total;
 };
@@ -90,8 +92,10 @@ WsLayout workspace_layout(const adaspa_problem* p) {
   // the 12 bytes per mass that callers' buffers are sized for.
   const size_t per_wg = (size_t)select_rows_per_wg((int)rows);
   const size_t parts = bh * ((nb + per_wg - 1) / per_wg) * nb;
-  const size_t sums = (parts > 4 * rows ? parts : 4 * rows) * sizeof(int64_t);
-  w.sums = off;   off = align_up(off + (sums > 12 * rows * nb ? sums : 12 * rows * nb));
+  size_t sums = (parts > 4 * rows ? parts : 4 * rows) * sizeof(int64_t);
+  sums = sums > 12 * rows * nb ? sums : 12 * rows * nb;
+  const size_t lse = key_split(p) ? bh * p->seqlen * sizeof(float) : 0;   // see adaspa_fused_online_search
+  w.sums = off;   off = align_up(off + (sums > lse ? sums : lse));
   w.headk = off;  off = align_up(off + bh * sizeof(int32_t));
   w.base = off;   off = align_up(off + bh * sizeof(int32_t));
   w.claim = off;  off = align_up(off + 9 * sizeof(uint32_t));   // mass-pass work queues (cleared as nine)
@@ -270,6 +274,7 @@ adaspa_status adaspa_dense_attn_lse(const adaspa_problem* prob, const void* q, c
   a.nkb = num_blocks(prob);
   a.scale = scale_of(prob);
   a.scale_log2 = a.scale * 1.4426950408889634f;
+  a.split = key_split(prob);
   a.claim = (uint32_t*)workspace;
   return launch_dense(a, prob->head_dim, (hipStream_t)stream) == hipSuccess ? ADASPA_OK : ADASPA_ERR_HIP;
 }
@@ -370,8 +375,14 @@ adaspa_status adaspa_fused_online_search(const adaspa_problem* prob, const void*
   a.nkb = num_blocks(prob);
   a.scale = scale_of(prob);
   a.scale_log2 = a.scale * 1.4426950408889634f;
+  a.split = key_split(prob);
   a.claim = (uint32_t*)((char*)workspace + wl.claim);
-  const MassParams m = mass_params(prob, q, k, lse, block_mass);
+  // Where the two passes are two launches, an LSE that the caller does not
+  // want is kept in the selection's part of the workspace, which is written
+  // only after the mass pass has read it.
+  if (a.split && lse == nullptr) a.lse = (float*)((char*)workspace + wl.sums);
+  MassParams m = mass_params(prob, q, k, a.lse, block_mass);
+  m.claim = a.claim;
   if (launch_fused_search(a, m, prob->head_dim, s) != hipSuccess) return ADASPA_ERR_HIP;
   return enqueue_selection(prob, sel, block_mass, row_ptr, col_idx, head_k, head_recall, workspace, s);
 }
@@ -444,6 +455,7 @@ adaspa_status adaspa_single_pass_online_search(const adaspa_problem* prob, const
     a.nkb = (int)nkb;
     a.scale = scale_of(prob);
     a.scale_log2 = a.scale * 1.4426950408889634f;
+    a.split = key_split(prob);
     a.claim = (uint32_t*)((char*)workspace + wl.claim);
     a.ylog = (float*)((char*)workspace + wl.total);
     a.ylse2 = (float*)((char*)workspace + wl.total + align_up((size_t)gn * nkb * L * sizeof(float)));
@@ -478,6 +490,7 @@ adaspa_status adaspa_block_sparse_attn(const adaspa_problem* prob, const void* q
   a.nkb = num_blocks(prob);
   a.scale = scale_of(prob);
   a.scale_log2 = a.scale * 1.4426950408889634f;
+  a.split = key_split(prob);
   a.claim = (uint32_t*)workspace;
   // Text query blocks keep every key block under the text sink, so they are
   // the longest rows; the kernel starts them first (the result does not

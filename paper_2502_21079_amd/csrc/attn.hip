@@ -971,6 +971,430 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_sparse_pair_ker
 }
 
 // ---------------------------------------------------------------------------
+// Key-split attention: dense, block-sparse (both block sizes) and the
+// attention pass of the single-pass search, for problems whose 256-row (or
+// one-block) workgroups would leave most of the chip idle.
+//
+// Such a launch takes as long as one workgroup's walk along its keys, at one
+// tile per step (a step is bound by its barrier and load latency long before
+// its MFMAs).  Here a workgroup of eight waves takes 64 query rows, two
+// groups of 32, and four waves share the keys of each group: 128-key units
+// go round the four splits, so a step covers four tiles and the walk is a
+// quarter as long.  A tile is 64 keys at d 64 and 32 at d 128: two ring slots
+// of four [K | V] tiles take 152 KB and 144 KB of the CU's 160 KB.  Each
+// wave is the pipeline of attn_fwd_kernel over its own tiles, with its own
+// softmax reference; at the end the four partial outputs of a row are scaled
+// to the largest reference and the row's whole sum (each to its share of the
+// result, so none can overflow) and added through LDS in split order.
+//
+// Which wave takes a tile depends only on the tile's place in the row's list
+// (dense: all tiles), so a row that keeps every block gives bit for bit the
+// dense result here too.  2,048 tokens x 2 heads, d 64: dense 33 -> 14 us,
+// block-sparse (20%, block 64) 29 -> 15 us; a step takes about 1.1 us, of which
+// the four tiles' loads are half and their latency most of the rest.
+// ---------------------------------------------------------------------------
+constexpr int kSplits = 4;            // waves that share a row's keys
+constexpr int kSplitRows = 64;        // query rows per workgroup
+
+template <int D, bool SPARSE, bool BS>
+__global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
+  static_assert(!(SPARSE && BS), "block masses come from the dense pass");
+  constexpr int NS = kSplits, RG = kSplitRows / 32, NT = 64 * NS * RG;
+  constexpr int G = D == 64 ? 2 : 1, KEYS = 32 * G;      // keys per tile
+  constexpr int UNIT = 128 / KEYS;                         // tiles per unit
+  using LD = KVLoader<D, RG, KEYS>;
+  using KDMA = typename LD::K;
+  using VDMA = typename LD::V;
+  constexpr int KS = KDMA::S, VS = VDMA::S;
+  constexpr int ND = D / 32, NK = D / 16;
+  __shared__ __attribute__((aligned(1024))) u16 sKV[2][NS][LD::ELEMS];   // ring slots of [K | V] tiles
+  __shared__ float sStat[4][NS][kSplitRows];               // partial references, sums
+  __shared__ int s_redo;
+
+  int bh, qt;                                              // head, 64-row tile
+  if constexpr (SPARSE) {
+    text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
+  } else {
+    const int lid = xcd_remap((int)blockIdx.x, a.n_items);
+    bh = lid / a.nqt;
+    qt = lid % a.nqt;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
+  const int rg = wave % RG, sp = wave / RG;                // row group, split
+  const int hw = lane >> 5, c32 = lane & 31;
+  const int gi = lane & 15, grp = lane >> 4;
+  const int L = a.seqlen;
+  const size_t hoff = (size_t)bh * L * D;
+  const uint32_t hbytes = (uint32_t)L * D * 2u;
+  const __amdgpu_buffer_rsrc_t rK = make_rsrc(a.k + hoff, hbytes);
+  const __amdgpu_buffer_rsrc_t rV = make_rsrc(a.v + hoff, hbytes);
+  const u32x4 rKw = rsrc_words(a.k + hoff, hbytes), rVw = rsrc_words(a.v + hoff, hbytes);
+  const int row0 = qt * kSplitRows;
+  const int qrow = row0 + rg * 32 + c32;
+  const int voff = ((4 * hw + (gi >> 2)) * VS) * 8 + 16 * (grp & 1) + 4 * (gi & 3);
+  const int klane = (c32 * KS + hw) * 8;
+
+  // The row's list (sparse), as in attn_fwd_kernel: its tiles, in list order,
+  // a ragged block elsewhere than at the end left out, out-of-range entries
+  // sending the whole row to the masked path.
+  int nf = L / KEYS;          // full tiles in the pipeline
+  int e0 = 0, ne = 0, skip = -1, skip_at = INT_MAX, rag_sub = 0;
+  bool slow = false;
+  const int bsh = (a.block == 128 ? 1 : 0) + (KEYS == 32 ? 1 : 0);   // log2 of the tiles per block
+  const int sub = 1 << bsh;
+  __amdgpu_buffer_rsrc_t rC = make_rsrc(a.col_idx, 0u);
+  auto load_chunk = [&](int c) -> int {
+    return __builtin_amdgcn_raw_buffer_load_b32(rC, (uint32_t)(c * 64 + lane) * 4u, 0, 0);
+  };
+  int c0 = 0, cid0 = 0, cid1 = 0;
+  if constexpr (SPARSE) {
+    const int64_t r = (int64_t)bh * a.nkb + row0 / a.block;
+    int64_t s = a.row_ptr[r], e = a.row_ptr[r + 1];
+    s = s < 0 ? 0 : (s > a.col_count ? a.col_count : s);
+    e = e < s ? s : (e > a.col_count ? a.col_count : e);
+    e0 = (int)s;
+    ne = (int)(e - s);
+    rC = make_rsrc(a.col_idx + e0, (uint32_t)ne * 4u);
+    cid0 = load_chunk(0);
+    cid1 = load_chunk(1);
+  }
+  bf16x8 qf[NK];
+  load_q<D>(a.q + hoff, qrow, L, hw, qf);
+  // Finite V where it is read before it is loaded: by the first step (against
+  // zero probabilities) and by a ragged tile's rows past the sequence.
+#pragma unroll
+  for (int s = 0; s < NS; ++s) zero_lds<VDMA::SLOTS>(sKV[1][s] + LD::VOFF, tid, NT);
+  zero_lds<VDMA::SLOTS>(sKV[0][0] + LD::VOFF, tid, NT);
+  if (tid == 0) s_redo = 0;
+  if constexpr (SPARSE) {
+    const bool ragged = L % a.block != 0;
+    for (int c = 0; c * 64 < ne; ++c) {
+      const int n = c * 64 + lane;
+      const int v = c == 0 ? cid0 : (c == 1 ? cid1 : load_chunk(c));
+      if (__any(n < ne && (v < 0 || v >= a.nkb))) slow = true;
+      const unsigned long long rb = __ballot(n < ne && ragged && v == a.nkb - 1);
+      if (skip < 0 && rb != 0ull) skip = c * 64 + __builtin_ctzll(rb);
+    }
+    if (!slow && skip >= 0 && skip == ne - 1) rag_sub = (L - (a.nkb - 1) * a.block) / KEYS;
+    nf = slow ? 0 : (ne - (skip >= 0 ? 1 : 0)) * sub + rag_sub;
+    skip_at = (skip >= 0 && skip != ne - 1) ? skip : INT_MAX;
+  }
+  // Tile t of the row belongs to split (t / UNIT) % NS; this wave's j-th tile
+  // is tile_of(j), j < n_mine.
+  auto owner = [](int t) { return (t / UNIT) % NS; };
+  auto tile_of = [&](int j) { return ((j / UNIT) * NS + sp) * UNIT + j % UNIT; };
+  auto count_of = [&](int s) {
+    const int u = nf / UNIT;
+    return (u / NS + (s < u % NS ? 1 : 0)) * UNIT + (s == u % NS ? nf % UNIT : 0);
+  };
+  const int n_mine = count_of(sp), n_steps = count_of(0);   // split 0 has the most
+  auto entry = [&](int t) -> int {     // CSR entry of tile t
+    const int i = t >> bsh;
+    return i + (i >= skip_at ? 1 : 0);
+  };
+  auto kbase = [&](int t) -> int {     // first key of tile t
+    if constexpr (!SPARSE) {
+      return t * KEYS;
+    } else {
+      const int i = entry(t);
+      const int v0 = __builtin_amdgcn_readlane(cid0, i & 63);
+      const int v1 = __builtin_amdgcn_readlane(cid1, i & 63);
+      return ((i >> 6) == c0 ? v0 : v1) * a.block + (t & (sub - 1)) * KEYS;
+    }
+  };
+
+  const float sl2 = a.scale_log2;
+  RowRef ref;
+  float lsum = 0.f;
+  // Block masses (BS), as in attn_fwd_kernel: a key block's tiles belong to
+  // one unit, so to one wave.
+  float bsum = 0.f, rowf = 0.f, bdone = 0.f;
+  int cdone = -1;
+  auto write_block = [&](float bs, int c) {
+    if constexpr (BS) {
+      float lo, hi;
+      half_pair(bs, lo, hi);
+      const float b = lo + hi;
+      float* col = a.ylog + ((size_t)bh * a.nkb + (size_t)__builtin_amdgcn_readfirstlane(c)) * (size_t)L;
+      if (hw == 0 && qrow < L) col[qrow] = (b > 0.f ? __builtin_amdgcn_logf(b) : -INFINITY) + ref.mc;
+    }
+  };
+  auto flush_block = [&](int c) {
+    if constexpr (BS) {
+      write_block(bsum, c);
+      bsum = 0.f;
+    }
+  };
+  auto flush_waiting = [&]() {
+    if constexpr (BS) {
+      if (cdone >= 0) {
+        write_block(bdone, cdone);
+        cdone = -1;
+      }
+    }
+  };
+  f32x16 o[ND];
+#pragma unroll
+  for (int d = 0; d < ND; ++d) o[d] = f32x16{};
+  bool redo = false;
+
+  if (nf > 0) {
+    if (n_mine > 0) {
+      KDMA::issue(rK, sKV[0][sp], kbase(tile_of(0)), rg, lane);
+      if (n_mine > 1) KDMA::issue(rK, sKV[1][sp], kbase(tile_of(1)), rg, lane);
+    }
+    wait_vmem();
+    __syncthreads();
+    f32x16 s_cur[2];
+    if (n_mine > 0) qk_tile<D, KS, G>(sKV[0][sp], qf, c32, hw, s_cur);
+    __syncthreads();            // slot 0 is refilled by step 0
+
+    bf16x8 p_prev[2][2];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) p_prev[g][s2] = bf16x8{};
+    bool pend = false;
+    float pend_alpha = 1.f;
+    RowSums rsum;
+    rsum.init(lane);
+    bool bad = false;
+    LD ld;
+    ld.init(rg, lane);
+    const u32x4 rMw = ld.mixed_v ? rVw : rKw;
+
+    // Step j of a wave is step t of attn_fwd_kernel on its own tiles.
+    auto step = [&](int j) {
+      const u16* rd = sKV[(j + 1) & 1][sp];
+      if (pend) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) o[d][e] *= pend_alpha;
+        pend = false;
+      }
+      const int t = tile_of(j);
+      uint32_t kbyte = (uint32_t)kbase(tile_of(j + 2 < n_mine ? j + 2 : n_mine - 1)) * (uint32_t)(D * 2);
+      uint32_t vbyte = (uint32_t)kbase(t) * (uint32_t)(D * 2);
+      if constexpr (SPARSE) {
+        // A wave's next tiles are at most a round of units (eight entries)
+        // ahead, so both stay inside the window of two chunks.
+        asm volatile("" : "+s"(kbyte), "+s"(vbyte));
+        if ((entry(t) >> 6) > c0) {
+          cid0 = cid1;
+          cid1 = load_chunk(c0 + 2);
+          ++c0;
+        }
+      }
+      uint32_t fill = lds_addr(sKV[j & 1][sp]);
+      asm volatile("" : "+s"(fill));
+      const uint32_t mbyte = ld.mixed_v ? vbyte : kbyte;
+      auto hook = [&](int slot) {       // loads in the first slots of the step
+        static_assert(LD::PW <= 2 * G * NK, "one load instruction per slot at most");
+        if (slot < LD::PW) ld.issue_n(slot, fill, rKw, rVw, rMw, kbyte, vbyte, mbyte);
+        if constexpr (BS)
+          if (slot == G * NK) flush_waiting();
+      };
+      f32x16 s_next[2];
+      bf16x8 p_cur[2][2];
+      float tsum = 0.f;
+      pipelined_step<D, KS, VS, G, BS, true>(hook, rd + klane, rd + LD::VOFF + voff, qf, s_cur, p_prev, s_next,
+                                             p_cur, o, sl2, ref.mc, rsum, &tsum);
+      move_reference<G, BS>(ref, rsum, bad, s_cur, p_cur, pend, pend_alpha, sl2, c32, false, &tsum);
+      if constexpr (BS) {
+        if (pend) {
+          bsum *= pend_alpha;
+          rowf *= pend_alpha;
+        }
+        bsum += tsum;
+        rowf += tsum;
+        if (((t + 1) & (sub - 1)) == 0) {
+          bdone = bsum;
+          cdone = t >> bsh;
+          bsum = 0.f;
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        s_cur[g] = s_next[g];
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) p_prev[g][s2] = p_cur[g][s2];
+      }
+    };
+    for (int j = 0; j < n_steps; ++j) {
+      if (j < n_mine) step(j);
+      wait_vmem();
+      __syncthreads();
+    }
+    if (n_mine > 0) {
+      flush_waiting();
+      if (pend) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) o[d][e] *= pend_alpha;
+      }
+      pv_tile<ND, VS, G>(sKV[(n_mine - 1) & 1][sp] + LD::VOFF + voff, p_prev, o);
+      lsum = finish_sums<G>(rsum, bad, p_prev, hw, c32);
+      bad = bad || !acc_finite<ND>(o);
+      redo = __any(bad);
+      if (redo && lane == 0) s_redo = 1;
+    }
+  }
+  __syncthreads();
+  const bool any_redo = s_redo != 0;
+  if (redo) {
+    ref = RowRef{};
+    lsum = 0.f;
+    bsum = 0.f;
+    rowf = 0.f;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) o[d] = f32x16{};
+  }
+
+  // Remaining tiles, one at a time with key masking, loaded by all waves and
+  // computed by those of one split (or by none that meet here).
+  using KAll = TileDMA<D, NS * RG, 1, KEYS>;
+  using VAll = TileDMA<D, NS * RG, 2, KEYS>;
+  auto masked_tile = [&](int kb, bool compute) {
+    KAll::issue(rK, sKV[0][0], kb, wave, lane);
+    VAll::issue(rV, sKV[0][0] + LD::VOFF, kb, wave, lane);
+    wait_vmem();
+    __syncthreads();
+    if (compute) {
+      f32x16 s[2];
+      qk_tile<D, KS, G>(sKV[0][0], qf, c32, hw, s);
+      mask_tile<G>(s, L - kb, hw);
+      bf16x8 pb[2][2];
+      float alpha;
+      if constexpr (BS) {
+        float fs;
+        alpha = softmax_tile_fsum<G>(s, ref, lsum, sl2, pb, fs);
+        bsum = bsum * alpha + fs;
+        rowf = rowf * alpha + fs;
+      } else {
+        alpha = softmax_tile<G>(s, ref, lsum, sl2, pb);
+      }
+#pragma unroll
+      for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[d][e] *= alpha;
+      pv_tile<ND, VS, G>(sKV[0][0] + LD::VOFF + voff, pb, o);
+    }
+    __syncthreads();
+  };
+  if constexpr (SPARSE) {
+    auto entry_tiles = [&](int i) {
+      const int c = a.col_idx[e0 + i];
+      if (c < 0 || c >= a.nkb) return;
+      for (int j = 0; j < sub; ++j) {
+        const int kb = c * a.block + j * KEYS;
+        if (kb >= L) break;
+        const bool left = slow || (i == skip && j >= rag_sub);
+        // What the pipeline left out of the end of a row continues its tiles;
+        // anything else it left out goes to split 0.
+        const int t = ((i - (i > skip_at ? 1 : 0)) << bsh) + j;
+        const int who = left ? (slow || skip_at != INT_MAX ? 0 : owner(nf)) : owner(t);
+        if (left || any_redo) masked_tile(kb, sp == who && (left || redo));
+      }
+    };
+    if (slow || any_redo) {
+      for (int i = 0; i < ne; ++i) entry_tiles(i);
+    } else if (skip >= 0) {
+      entry_tiles(skip);
+    }
+  } else {
+    if (any_redo)
+      for (int t = 0; t < nf; ++t) {
+        const bool mine = redo && owner(t) == sp;
+        masked_tile(t * KEYS, mine);
+        if (mine && ((t + 1) & (sub - 1)) == 0) flush_block(t >> bsh);
+      }
+    if (nf * KEYS < L) masked_tile(nf * KEYS, owner(nf) == sp);
+    if (owner(nf) == sp && (nf * KEYS < L || (nf & (sub - 1)) != 0)) flush_block(nf >> bsh);
+  }
+
+  // The row's reference and sum over the splits, and this wave's share.
+  float lt;
+  {
+    float lo, hi;
+    half_pair(lsum, lo, hi);
+    lt = lo + hi;
+  }
+  const int r = rg * 32 + c32;
+  if (hw == 0) {
+    sStat[0][sp][r] = ref.m == -INFINITY ? -INFINITY : ref.mc;
+    sStat[1][sp][r] = ref.m;
+    sStat[2][sp][r] = lt;
+  }
+  if constexpr (BS) {
+    float lo, hi;
+    half_pair(rowf, lo, hi);
+    if (hw == 0) sStat[3][sp][r] = lo + hi;
+  }
+  __syncthreads();
+  float mc = -INFINITY, m = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    mc = fmaxf(mc, sStat[0][s][r]);
+    m = fmaxf(m, sStat[1][s][r]);
+  }
+  float total = 0.f, totalf = 0.f, mine = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const float ms = sStat[0][s][r];
+    const float f = ms == -INFINITY ? 0.f : fast_exp2(ms - mc);
+    total += f * sStat[2][s][r];
+    if constexpr (BS) totalf += f * sStat[3][s][r];
+    mine = s == sp ? f : mine;
+  }
+  if (sp == 0 && hw == 0 && qrow < L) {
+    if (a.lse != nullptr)
+      a.lse[(size_t)bh * L + qrow] = total > 0.f ? fmaf(m, a.scale, logf(total)) : -INFINITY;
+    if constexpr (BS)
+      a.ylse2[(size_t)bh * L + qrow] = totalf > 0.f ? mc + __builtin_amdgcn_logf(totalf) : INFINITY;
+  }
+  mine *= total > 0.f ? 1.f / total : 0.f;
+  // Partial outputs to LDS (the ring is free: every wave has passed the
+  // barrier after its last read), then each thread adds whole 16-byte pieces.
+  constexpr int RS = D + 4;
+  static_assert(NS * kSplitRows * RS * 4 <= (int)sizeof(sKV), "the partial outputs fit the ring");
+  float* part = reinterpret_cast<float*>(&sKV[0][0][0]);
+#pragma unroll
+  for (int d = 0; d < ND; ++d)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = o[d][4 * i + j] * mine;
+      *reinterpret_cast<f32x4*>(part + (sp * kSplitRows + r) * RS + d * 32 + 8 * i + 4 * hw) = v;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int c = tid; c < kSplitRows * D / 8; c += NT) {
+    const int pr = c / (D / 8), ch = c % (D / 8);
+    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const f32x4* p = reinterpret_cast<const f32x4*>(part + (s * kSplitRows + pr) * RS + ch * 8);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lo[j] += p[0][j];
+        hi[j] += p[1][j];
+      }
+    }
+    bf16x8 w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      w[j] = (__bf16)lo[j];
+      w[4 + j] = (__bf16)hi[j];
+    }
+    if (row0 + pr < L) *reinterpret_cast<bf16x8*>(a.o + hoff + (size_t)(row0 + pr) * D + ch * 8) = w;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Block attention mass: W[p][c] = sum_{i in p, j in c} exp(scale*q_i.k_j - LSE_i)
 //
 // One workgroup of eight waves (32 rows each) covers 256 query rows: QB
@@ -1335,7 +1759,28 @@ static hipError_t launch_attn(const AttnParams& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Key-split launch: one workgroup per 64 query rows, text rows first if sparse.
+template <bool SPARSE, bool BS>
+static hipError_t launch_split(AttnParams a, int D, hipStream_t st) {
+  a.nqt = (a.seqlen + kSplitRows - 1) / kSplitRows;
+  a.n_items = a.nqt * a.batch_heads;
+  if (SPARSE) {
+    const int per = a.block / kSplitRows;     // 64-row tiles per query block
+    a.tq0 *= per;
+    a.tq1 = a.tq1 * per < a.nqt ? a.tq1 * per : a.nqt;
+    if (a.tq1 - a.tq0 >= a.nqt) a.tq0 = a.tq1 = 0;
+  }
+  if (D == 64) hipLaunchKernelGGL((attn_split_kernel<64, SPARSE, BS>), dim3(a.n_items), dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((attn_split_kernel<128, SPARSE, BS>), dim3(a.n_items), dim3(512), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
+  if (a.split) {
+    a.row_ptr = nullptr;
+    a.col_idx = nullptr;
+    return launch_split<false, false>(a, D, st);
+  }
   // 256 query rows per workgroup (eight waves of 32 rows): every K/V tile
   // brought into LDS serves twice the rows of a 128-row workgroup.
   a.row_ptr = nullptr;
@@ -1373,6 +1818,7 @@ static hipError_t plan_sparse_items(AttnParams& a, hipStream_t st) {
 }
 
 hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
+  if (a.split) return launch_split<true, false>(a, D, st);
   if (a.block == 64) {
     // One workgroup per pair of query blocks (128 rows); text ranges in pairs.
     a.nqt = (a.nkb + 1) / 2;
@@ -1436,6 +1882,10 @@ static hipError_t launch_mass_t(MassParams a, hipStream_t st) {
 }
 
 hipError_t launch_fused_search(AttnParams a, MassParams m, int D, hipStream_t st) {
+  if (a.split) {                // the mass pass of its own fills the chip too
+    const hipError_t e = launch_dense(a, D, st);
+    return e != hipSuccess ? e : launch_block_mass(m, D, st);
+  }
   // Work items as in launch_dense: (head, 256-row query tile), which is also
   // the mass pass's (head, group of 256 / block query blocks).
   a.row_ptr = nullptr;
@@ -1462,11 +1912,21 @@ hipError_t launch_fused_search(AttnParams a, MassParams m, int D, hipStream_t st
   return hipGetLastError();
 }
 
+static hipError_t launch_single_pass_reduce(const AttnParams& a, hipStream_t st) {
+  hipLaunchKernelGGL(single_pass_reduce_kernel, dim3((a.nkb + kReduceWaves - 1) / kReduceWaves, a.batch_heads),
+                     dim3(64 * kReduceWaves), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_single_pass_search(AttnParams a, int D, hipStream_t st) {
-  // Work items as in launch_dense: (head, 256-row query tile), two query
-  // blocks of 128 or four of 64.
   a.row_ptr = nullptr;
   a.col_idx = nullptr;
+  if (a.split) {
+    const hipError_t e = launch_split<false, true>(a, D, st);
+    return e != hipSuccess ? e : launch_single_pass_reduce(a, st);
+  }
+  // Work items as in launch_dense: (head, 256-row query tile), two query
+  // blocks of 128 or four of 64.
   a.nqt = (a.seqlen + 255) / 256;
   a.n_items = a.nqt * a.batch_heads;
   a.n_wg = a.n_items;
@@ -1479,10 +1939,7 @@ hipError_t launch_single_pass_search(AttnParams a, int D, hipStream_t st) {
   if (D == 64) hipLaunchKernelGGL((single_pass_search_kernel<64>), dim3(a.n_wg), dim3(512), 0, st, a);
   else hipLaunchKernelGGL((single_pass_search_kernel<128>), dim3(a.n_wg), dim3(512), 0, st, a);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(single_pass_reduce_kernel, dim3((a.nkb + kReduceWaves - 1) / kReduceWaves, a.batch_heads),
-                     dim3(64 * kReduceWaves), 0, st, a);
-  return hipGetLastError();
+  return e != hipSuccess ? e : launch_single_pass_reduce(a, st);
 }
 
 hipError_t launch_block_mass(MassParams a, int D, hipStream_t st) {

@@ -78,16 +78,17 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // banks; the V tile has two, so each group of 4 rows x 32 bytes read by a
 // transposed load covers distinct banks.  With constant strides every operand
 // address is one lane base plus a compile-time offset.
-template <int D, int NW, int PADC>
+// KEYS is 64 (KT), or 32 for the key-split attention kernel's d 128 tiles.
+template <int D, int NW, int PADC, int KEYS = KT>
 struct TileDMA {
   static constexpr int CPR = D / 8;                 // data chunks per row
   static constexpr int S = CPR + PADC;              // chunks per LDS row
-  static constexpr int SLOTS = KT * S;              // chunk slots per tile
-  static constexpr int NINST = SLOTS / 64;          // 64-slot DMA instructions
-  static_assert(SLOTS % 64 == 0, "tile slots must fill whole instructions");
+  static constexpr int NINST = (KEYS * S + 63) / 64;   // 64-slot DMA instructions
+  static constexpr int SLOTS = NINST * 64;          // chunk slots per tile, the last ones past its rows if
+                                                    // they do not fill whole instructions
   static constexpr int ELEMS = SLOTS * 8;           // bf16 elements per tile
 
-  // Issue the loads of rows [kbase, kbase + KT).  Rows past the buffer's end
+  // Issue the loads of rows [kbase, kbase + KEYS).  Rows past the buffer's end
   // and pad slots use an out-of-range offset: the load is skipped and the slot
   // reads zero.
   __device__ __forceinline__ static void issue(__amdgpu_buffer_rsrc_t r, u16* dst, int kbase,
@@ -128,7 +129,7 @@ struct TileDMA {
   // duplicate keeps every offset below 2^16).
   __device__ __forceinline__ static uint32_t rel_offset(int i, int lane) {
     const int p = i * 64 + lane;
-    const int row = p / S, ch = p % S;
+    const int row = p / S < KEYS ? p / S : KEYS - 1, ch = p % S;
     return (uint32_t)(row * D + (ch < CPR ? ch : CPR - 1) * 8) * 2u;
   }
   // Instruction i of a full tile whose first byte is tile_byte: the offset
@@ -188,10 +189,10 @@ struct KLoader {
 // Entries j with (j+1)*NW <= K::NINST are K loads for every wave, entries
 // with j*NW >= K::NINST are V loads for every wave, and the one j in between
 // (if any) is K for some waves and V for the others ("mixed").
-template <int D, int NW>
+template <int D, int NW, int KEYS = KT>
 struct KVLoader {
-  using K = TileDMA<D, NW, 1>;
-  using V = TileDMA<D, NW, 2>;
+  using K = TileDMA<D, NW, 1, KEYS>;
+  using V = TileDMA<D, NW, 2, KEYS>;
   static constexpr int NK = K::NINST;
   static constexpr int NTOT = K::NINST + V::NINST;
   static constexpr int PW = (NTOT + NW - 1) / NW;           // loads per wave and step
@@ -332,9 +333,10 @@ __device__ __forceinline__ void qk_tile(const u16* sK, const bf16x8 (&qf)[D / 16
   }
 }
 
+template <int G = 2>
 __device__ __forceinline__ void mask_tile(f32x16 (&s)[2], int kvalid, int hw) {
 #pragma unroll
-  for (int g = 0; g < 2; ++g)
+  for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int key = 32 * g + 8 * (e >> 2) + 4 * hw + (e & 3);
@@ -541,14 +543,15 @@ __device__ __forceinline__ bool acc_finite(const f32x16 (&o)[ND]) {
 // current reference, moved first if this tile needs it.  Returns the factor
 // by which the output accumulator must be rescaled before this tile's P V
 // (1 when the reference did not move); lsum includes the tile afterwards.
+template <int G = 2>
 __device__ __forceinline__ float softmax_tile(const f32x16 (&s)[2], RowRef& ref, float& lsum, float sl2,
                                               bf16x8 (&pb)[2][2]) {
-  float ts = exp_tile(s, sl2, ref.mc, pb);
+  float ts = exp_tile<G>(s, sl2, ref.mc, pb);
   float a = 1.f;
   if (__any(ts > ref.lim)) {
-    a = ref.raise(s, sl2);
+    a = ref.template raise<G>(s, sl2);
     lsum *= a;
-    ts = exp_tile(s, sl2, ref.mc, pb);
+    ts = exp_tile<G>(s, sl2, ref.mc, pb);
   }
   lsum += ts;
   return a;
@@ -556,14 +559,15 @@ __device__ __forceinline__ float softmax_tile(const f32x16 (&s)[2], RowRef& ref,
 
 // As softmax_tile; fsum receives this lane's fp32 sum of the tile's
 // exponentials against the reference they were finally taken against.
+template <int G = 2>
 __device__ __forceinline__ float softmax_tile_fsum(const f32x16 (&s)[2], RowRef& ref, float& lsum, float sl2,
                                                    bf16x8 (&pb)[2][2], float& fsum) {
-  float ts = exp_tile_fsum(s, sl2, ref.mc, pb, fsum);
+  float ts = exp_tile_fsum<G>(s, sl2, ref.mc, pb, fsum);
   float a = 1.f;
   if (__any(ts > ref.lim)) {
-    a = ref.raise(s, sl2);
+    a = ref.template raise<G>(s, sl2);
     lsum *= a;
-    ts = exp_tile_fsum(s, sl2, ref.mc, pb, fsum);
+    ts = exp_tile_fsum<G>(s, sl2, ref.mc, pb, fsum);
   }
   lsum += ts;
   return a;

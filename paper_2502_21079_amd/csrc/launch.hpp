@@ -28,6 +28,7 @@ struct AttnParams {
   int tq0, tq1;               // sparse: text query blocks [tq0, tq1), dispatched first
   int kb_guess, n_guess;      // sparse: first text block and the text block count (-1, 0: none),
                               // whose tiles every row begins with under the text sink
+  bool split;                 // the key-split kernel takes the problem (use_key_split)
   uint32_t* claim;            // 9 work-queue counters (one per XCD + a flag), or null
   int n_items;                // work items: (head, query tile) or (head, query block / pair)
   int n_static;               // sparse: items [0, n_static) run in the static order
@@ -38,6 +39,19 @@ struct AttnParams {
   float* ylse2;
   float* wmass;
 };
+
+// Whether attention over batch_heads sequences of length seqlen runs in the
+// key-split kernel (64 query rows per workgroup): by the shape alone, so that
+// every entry point takes a problem the same way and their results agree bit
+// for bit.  512 such workgroups run in two rounds on 256 CUs; up to there the
+// key split is the faster one (8,192 tokens, dense, us, one-tile-per-step
+// kernels against key split: 2 heads = 256 workgroups 113 -> 48 at d 64 and
+// 154 -> 83 at d 128; 4 heads = 512 workgroups 114 -> 92 and 160 -> 159; but 6
+// heads 132 -> 136 and 193 -> 239).
+constexpr int64_t kSplitMaxTiles = 512;
+inline bool use_key_split(int64_t batch_heads, int seqlen) {
+  return batch_heads * ((seqlen + 63) / 64) <= kSplitMaxTiles;
+}
 
 struct MassParams {
   const u16* q;
@@ -95,9 +109,9 @@ struct SelectParams {
 hipError_t launch_dense(AttnParams a, int head_dim, hipStream_t st);
 hipError_t launch_sparse(AttnParams a, int head_dim, hipStream_t st);
 hipError_t launch_block_mass(MassParams a, int head_dim, hipStream_t st);
-// Dense attention + LSE and the block masses of the same rows in one launch
-// (a: the attention's arguments with a.claim the optional work-queue
-// counters; m: the mass pass's, its lse unused).
+// Dense attention + LSE and the block masses of the same rows, in one launch
+// or, where a.split, in two (m.lse then is a.lse) (a: the attention's arguments with a.claim the optional work-queue
+// counters; m: the mass pass's, its lse otherwise unused).
 hipError_t launch_fused_search(AttnParams a, MassParams m, int head_dim, hipStream_t st);
 // Dense attention + LSE and the block masses of its LSE in one pass over
 // Q K^T (a.ylog, a.ylse2: scratch of B*H*nkb*L and B*H*L floats; a.wmass:
