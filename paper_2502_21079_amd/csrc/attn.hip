@@ -65,6 +65,40 @@ struct NoTail {
   __device__ __forceinline__ void operator()(T&&...) const {}
 };
 
+// Block-sparse problems between the two ways (more tiles of 64 query rows than
+// use_key_split takes, with a text range).  When the text query rows keep
+// several times the blocks of the average row, they are the critical path of
+// the kernels that walk a row in one workgroup: about `walk` us for each 64
+// keys of the sequence and 8 more.  The key-split kernel walks them four times
+// as fast, but takes its 256 workgroups at a time, each for about `tile` us
+// for every 64 keys of its row's list and `fixed` more (fitted to 8,192 to
+// 32,768 tokens, 768 to 2,048 tiles, 4 to 30% kept; at 10%, one way against
+// the other: 16,384 tokens x 4 heads 168 -> 86 us at d 64 and 226 -> 154 us at
+// d 128, 8,192 tokens x 12 heads 89 -> 80 and 121 -> 117).  Only the device
+// knows the lists' lengths, so both kernels are launched and the one that is
+// not to run returns at once (1-3 us).
+constexpr int kPickMaxTiles = 4096;
+struct PickCost {
+  int walk, tile, fixed;      // in units of 1/100 us
+};
+__host__ __device__ constexpr PickCost pick_cost(int head_dim) {
+  return head_dim == 64 ? PickCost{72, 29, 700} : PickCost{92, 55, 800};
+}
+// Whether the split kernel is expected to be faster by 15% and more, the rows'
+// lists adding up to nnz64 times 64 keys over `rows` lists.
+__host__ __device__ inline bool split_pays(PickCost c, int64_t tiles, int64_t nf, int64_t nnz64, int64_t rows) {
+  return tiles * (c.tile * nnz64 + c.fixed * rows) / 20 * 23 < 256 * rows * (c.walk * nf + 800);
+}
+template <int D>
+__device__ __forceinline__ bool pick_key_split(const AttnParams& a) {
+  const int64_t rows = (int64_t)a.batch_heads * a.nkb;
+  const int64_t end = a.row_ptr[rows];
+  const int64_t nnz = end < 0 ? 0 : (end > a.col_count ? a.col_count : end);
+  const int64_t text = (int64_t)a.row_ptr[a.text_block + 1] - a.row_ptr[a.text_block];
+  return text * rows >= 3 * nnz && split_pays(pick_cost(D), (int64_t)a.batch_heads * ((a.seqlen + 63) / 64),
+                                              a.seqlen / 64, nnz * (a.block / 64), rows);
+}
+
 // With BS (dense only) the body also writes, for every row and key block c,
 // log2 of the row's unnormalised mass in block c plus the row's reference at
 // that time, so that the block's share of the row's softmax is
@@ -95,6 +129,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   // is given.
   int bh, qt;
   if constexpr (SPARSE) {
+    if (a.pick == PICK_OTHERS && pick_key_split<D>(a)) return;
     int item = (int)blockIdx.x;
     if (item >= a.n_static) {                // the queued tail (see claim_item)
       __shared__ int s_tail;
@@ -553,6 +588,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_sparse_pair_ker
 
   int bh, pq;
   {
+    if (a.pick == PICK_OTHERS && pick_key_split<D>(a)) return;
     int item = (int)blockIdx.x;
     if (item >= a.n_static) {                // as in attn_fwd_kernel
       __shared__ int s_tail;
@@ -1013,6 +1049,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
 
   int bh, qt;                                              // head, 64-row tile
   if constexpr (SPARSE) {
+    if (a.pick == PICK_SPLIT && !pick_key_split<D>(a)) return;
     text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
   } else {
     const int lid = xcd_remap((int)blockIdx.x, a.n_items);
@@ -1819,6 +1856,17 @@ static hipError_t plan_sparse_items(AttnParams& a, hipStream_t st) {
 
 hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   if (a.split) return launch_split<true, false>(a, D, st);
+  const int64_t tiles = (int64_t)a.batch_heads * ((a.seqlen + kSplitRows - 1) / kSplitRows);
+  const int64_t nf = a.seqlen / 64, rows = (int64_t)a.batch_heads * a.nkb, all = rows * a.nkb;
+  const int64_t nnz = a.col_count < all ? a.col_count : all / 100 * 12;
+  if (a.tq1 > a.tq0 && tiles <= kPickMaxTiles &&
+      split_pays(pick_cost(D), tiles, nf, nnz * (a.block / 64), rows)) {    // see pick_key_split
+    a.pick = PICK_SPLIT;
+    const hipError_t e = launch_split<true, false>(a, D, st);
+    if (e != hipSuccess) return e;
+    a.pick = PICK_OTHERS;
+    if (tiles <= 1024) a.claim = nullptr;     // one row per workgroup slot: nothing to balance
+  }
   if (a.block == 64) {
     // One workgroup per pair of query blocks (128 rows); text ranges in pairs.
     a.nqt = (a.nkb + 1) / 2;

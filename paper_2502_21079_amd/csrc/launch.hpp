@@ -8,6 +8,9 @@ namespace adaspa {
 
 typedef uint16_t u16;
 
+// Every pattern, only those that the key-split kernel is to take, only the others.
+enum { PICK_ALL = 0, PICK_SPLIT = 1, PICK_OTHERS = 2 };
+
 struct AttnParams {
   const u16* q;
   const u16* k;
@@ -29,6 +32,8 @@ struct AttnParams {
   int kb_guess, n_guess;      // sparse: first text block and the text block count (-1, 0: none),
                               // whose tiles every row begins with under the text sink
   bool split;                 // the key-split kernel takes the problem (use_key_split)
+  int pick;                   // sparse: which patterns a launch runs (PICK_*, set by the launcher)
+  int text_block;             // sparse: the first text block (with PICK_*)
   uint32_t* claim;            // 9 work-queue counters (one per XCD + a flag), or null
   int n_items;                // work items: (head, query tile) or (head, query block / pair)
   int n_static;               // sparse: items [0, n_static) run in the static order
