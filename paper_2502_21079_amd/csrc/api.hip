@@ -78,6 +78,10 @@ adaspa_status check_select(const adaspa_problem* p, const adaspa_select* s) {
 
 bool key_split(const adaspa_problem* p) { return use_key_split((int64_t)p->batch * p->heads, p->seqlen); }
 
+int key_split_tail(const adaspa_problem* p) {
+  return split_tail((int64_t)p->batch * p->heads, p->seqlen, p->head_dim);
+}
+
 struct WsLayout {
   size_t sums, headk, base, claim, total;
 };
@@ -94,7 +98,8 @@ WsLayout workspace_layout(const adaspa_problem* p) {
   const size_t parts = bh * ((nb + per_wg - 1) / per_wg) * nb;
   size_t sums = (parts > 4 * rows ? parts : 4 * rows) * sizeof(int64_t);
   sums = sums > 12 * rows * nb ? sums : 12 * rows * nb;
-  const size_t lse = key_split(p) ? bh * p->seqlen * sizeof(float) : 0;   // see adaspa_fused_online_search
+  const bool two = key_split(p) || key_split_tail(p) > 0;                 // see adaspa_fused_online_search
+  const size_t lse = two ? bh * p->seqlen * sizeof(float) : 0;
   w.sums = off;   off = align_up(off + (sums > lse ? sums : lse));
   w.headk = off;  off = align_up(off + bh * sizeof(int32_t));
   w.base = off;   off = align_up(off + bh * sizeof(int32_t));
@@ -275,6 +280,7 @@ adaspa_status adaspa_dense_attn_lse(const adaspa_problem* prob, const void* q, c
   a.scale = scale_of(prob);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   a.split = key_split(prob);
+  a.n_tail = key_split_tail(prob);
   a.claim = (uint32_t*)workspace;
   return launch_dense(a, prob->head_dim, (hipStream_t)stream) == hipSuccess ? ADASPA_OK : ADASPA_ERR_HIP;
 }
@@ -376,11 +382,12 @@ adaspa_status adaspa_fused_online_search(const adaspa_problem* prob, const void*
   a.scale = scale_of(prob);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   a.split = key_split(prob);
+  a.n_tail = key_split_tail(prob);
   a.claim = (uint32_t*)((char*)workspace + wl.claim);
   // Where the two passes are two launches, an LSE that the caller does not
   // want is kept in the selection's part of the workspace, which is written
   // only after the mass pass has read it.
-  if (a.split && lse == nullptr) a.lse = (float*)((char*)workspace + wl.sums);
+  if ((a.split || a.n_tail > 0) && lse == nullptr) a.lse = (float*)((char*)workspace + wl.sums);
   MassParams m = mass_params(prob, q, k, a.lse, block_mass);
   m.claim = a.claim;
   if (launch_fused_search(a, m, prob->head_dim, s) != hipSuccess) return ADASPA_ERR_HIP;
@@ -456,6 +463,10 @@ adaspa_status adaspa_single_pass_online_search(const adaspa_problem* prob, const
     a.scale = scale_of(prob);
     a.scale_log2 = a.scale * 1.4426950408889634f;
     a.split = key_split(prob);
+    // The tail's items are the last ones of all pairs: this group's share.
+    const int64_t nqt = ((int64_t)L + 255) / 256, first = bh_all * nqt - key_split_tail(prob);
+    const int64_t tail = (g0 + gn) * nqt - first;
+    a.n_tail = tail <= 0 ? 0 : (int)(tail < gn * nqt ? tail : gn * nqt);
     a.claim = (uint32_t*)((char*)workspace + wl.claim);
     a.ylog = (float*)((char*)workspace + wl.total);
     a.ylse2 = (float*)((char*)workspace + wl.total + align_up((size_t)gn * nkb * L * sizeof(float)));

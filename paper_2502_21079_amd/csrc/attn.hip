@@ -1052,9 +1052,17 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
     if (a.pick == PICK_SPLIT && !pick_key_split<D>(a)) return;
     text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
   } else {
-    const int lid = xcd_remap((int)blockIdx.x, a.n_items);
-    bh = lid / a.nqt;
-    qt = lid % a.nqt;
+    int lid = xcd_remap((int)blockIdx.x, a.n_items);
+    if (a.n_tail > 0) {          // the last n_tail of a launch's 256-row items, four tiles each
+      const int nqt = (a.seqlen + 255) / 256;
+      const int item = a.batch_heads * nqt - a.n_tail + lid / 4;
+      bh = item / nqt;
+      qt = (item % nqt) * 4 + lid % 4;
+      if (qt >= a.nqt) return;
+    } else {
+      bh = lid / a.nqt;
+      qt = lid % a.nqt;
+    }
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
@@ -1800,7 +1808,7 @@ static hipError_t launch_attn(const AttnParams& a, hipStream_t st) {
 template <bool SPARSE, bool BS>
 static hipError_t launch_split(AttnParams a, int D, hipStream_t st) {
   a.nqt = (a.seqlen + kSplitRows - 1) / kSplitRows;
-  a.n_items = a.nqt * a.batch_heads;
+  a.n_items = a.n_tail > 0 ? 4 * a.n_tail : a.nqt * a.batch_heads;
   if (SPARSE) {
     const int per = a.block / kSplitRows;     // 64-row tiles per query block
     a.tq0 *= per;
@@ -1813,18 +1821,20 @@ static hipError_t launch_split(AttnParams a, int D, hipStream_t st) {
 }
 
 hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
-  if (a.split) {
-    a.row_ptr = nullptr;
-    a.col_idx = nullptr;
-    return launch_split<false, false>(a, D, st);
+  a.row_ptr = nullptr;
+  a.col_idx = nullptr;
+  if (a.split) return launch_split<false, false>(a, D, st);
+  if (a.n_tail > 0) {
+    const hipError_t e = launch_split<false, false>(a, D, st);
+    if (e != hipSuccess) return e;
   }
   // 256 query rows per workgroup (eight waves of 32 rows): every K/V tile
   // brought into LDS serves twice the rows of a 128-row workgroup.
-  a.row_ptr = nullptr;
-  a.col_idx = nullptr;
   a.nqt = (a.seqlen + 255) / 256;
-  a.n_items = a.nqt * a.batch_heads;
+  a.n_items = a.nqt * a.batch_heads - a.n_tail;
+  if (a.n_items == 0) return hipSuccess;
   a.n_wg = a.n_items;
+  if (a.n_items <= 256) a.claim = nullptr;      // all run at once: nothing to balance
   if (a.claim != nullptr) {
     // A quarter more workgroups than items: the XCDs that run ahead take the
     // items the others have not reached; surplus workgroups find every queue
@@ -1930,7 +1940,7 @@ static hipError_t launch_mass_t(MassParams a, hipStream_t st) {
 }
 
 hipError_t launch_fused_search(AttnParams a, MassParams m, int D, hipStream_t st) {
-  if (a.split) {                // the mass pass of its own fills the chip too
+  if (a.split || a.n_tail > 0) {
     const hipError_t e = launch_dense(a, D, st);
     return e != hipSuccess ? e : launch_block_mass(m, D, st);
   }
@@ -1969,15 +1979,17 @@ static hipError_t launch_single_pass_reduce(const AttnParams& a, hipStream_t st)
 hipError_t launch_single_pass_search(AttnParams a, int D, hipStream_t st) {
   a.row_ptr = nullptr;
   a.col_idx = nullptr;
-  if (a.split) {
+  if (a.split || a.n_tail > 0) {
     const hipError_t e = launch_split<false, true>(a, D, st);
-    return e != hipSuccess ? e : launch_single_pass_reduce(a, st);
+    if (e != hipSuccess) return e;
   }
   // Work items as in launch_dense: (head, 256-row query tile), two query
   // blocks of 128 or four of 64.
   a.nqt = (a.seqlen + 255) / 256;
-  a.n_items = a.nqt * a.batch_heads;
+  a.n_items = a.split ? 0 : a.nqt * a.batch_heads - a.n_tail;
+  if (a.n_items == 0) return launch_single_pass_reduce(a, st);
   a.n_wg = a.n_items;
+  if (a.n_items <= 256) a.claim = nullptr;
   if (a.claim != nullptr) {
     a.n_wg = a.n_items + (a.n_items + 3) / 4;
     hipLaunchKernelGGL(claim_reset_kernel, dim3(1), dim3(64), 0, st, a.claim);

@@ -32,6 +32,7 @@ struct AttnParams {
   int kb_guess, n_guess;      // sparse: first text block and the text block count (-1, 0: none),
                               // whose tiles every row begins with under the text sink
   bool split;                 // the key-split kernel takes the problem (use_key_split)
+  int n_tail;                 // dense: the last items of this launch that run key-split (split_tail)
   int pick;                   // sparse: which patterns a launch runs (PICK_*, set by the launcher)
   int text_block;             // sparse: the first text block (with PICK_*)
   uint32_t* claim;            // 9 work-queue counters (one per XCD + a flag), or null
@@ -56,6 +57,24 @@ struct AttnParams {
 constexpr int64_t kSplitMaxTiles = 512;
 inline bool use_key_split(int64_t batch_heads, int seqlen) {
   return batch_heads * ((seqlen + 63) / 64) <= kSplitMaxTiles;
+}
+
+// Beyond that, dense attention runs one (head, 256-row tile) item per CU at a
+// time.  When the items leave a last round of few items, those run key-split
+// instead, four workgroups each: the number of such items, always the last
+// ones.  Up to 64 items fill one round of the split kernel, about a third of a
+// whole round, and at d 64 two thirds for up to 128, where a nearly empty
+// round of whole items takes 0.65 (d 128) and 0.77 (d 64) of a full one.  After
+// many rounds the CUs no longer end together and the last items hide among the
+// others' ends, so this stops at five whole rounds.  Dense, us, before and
+// after: 8,192 tokens x 9 heads (one round and 32 items) 240 -> 178 at d 64 and
+// 357 -> 291 at d 128; 35,000 x 4 (two and 36) 1492 -> 1282 and 2362 -> 2121;
+// 11,000 x 24 (four and 8) 819 -> 778 and 1284 -> 1276; but 17,920 x 48
+// (thirteen and 32, d 64) 3825 -> 3932.
+inline int split_tail(int64_t batch_heads, int seqlen, int head_dim) {
+  const int64_t n = batch_heads * ((seqlen + 255) / 256), rest = n % 256;
+  if (use_key_split(batch_heads, seqlen) || n < 256 || n / 256 > 5) return 0;
+  return rest <= (head_dim == 64 ? 128 : 64) ? (int)rest : 0;
 }
 
 struct MassParams {
@@ -115,7 +134,7 @@ hipError_t launch_dense(AttnParams a, int head_dim, hipStream_t st);
 hipError_t launch_sparse(AttnParams a, int head_dim, hipStream_t st);
 hipError_t launch_block_mass(MassParams a, int head_dim, hipStream_t st);
 // Dense attention + LSE and the block masses of the same rows, in one launch
-// or, where a.split, in two (m.lse then is a.lse) (a: the attention's arguments with a.claim the optional work-queue
+// or, where a.split or a.n_tail, in two (m.lse then is a.lse) (a: the attention's arguments with a.claim the optional work-queue
 // counters; m: the mass pass's, its lse otherwise unused).
 hipError_t launch_fused_search(AttnParams a, MassParams m, int head_dim, hipStream_t st);
 // Dense attention + LSE and the block masses of its LSE in one pass over
