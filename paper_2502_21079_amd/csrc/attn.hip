@@ -320,6 +320,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
     __syncthreads();
     f32x16 s_cur[2];
     qk_tile<D, KS>(sK[0], qf, c32, hw, s_cur);
+    ref.raise(s_cur, sl2);      // the rows' first reference
     __syncthreads();            // slot 0 is refilled by step 0
 
     bf16x8 p_prev[2][2];
@@ -396,7 +397,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
       float tsum = 0.f;
       pipelined_step<D, KS, VS, 2, BS, !SPARSE>(hook, rdK + klane, rdV + voff, qf, s_cur, p_prev, s_next, p_cur, o,
                                        sl2, ref.mc, rsum, &tsum);
-      move_reference<2, BS>(ref, rsum, bad, s_cur, p_cur, pend, pend_alpha, sl2, c32, false, &tsum);
+      move_reference<2, BS>(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32, &tsum);
       if constexpr (BS) {
         if (pend) {                     // the reference moved at this tile
           bsum *= pend_alpha;
@@ -436,7 +437,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
     }
     pv_tile<ND, VS>(sV[(nf - 1) & (RING - 1)] + voff, p_prev, o);
     lsum = finish_sums(rsum, bad, p_prev, hw, c32);
-    bad = bad || !acc_finite<ND>(o);
+    bad = bad || ref.m == -INFINITY || !acc_finite<ND>(o);
     redo = __any(bad);
     if (redo && lane == 0) s_redo = 1;
     __syncthreads();
@@ -539,8 +540,22 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   }
 }
 
+// Waves per SIMD that a kernel's registers are held to.  At d 64 the pipeline
+// fits 168 of them, so three workgroups of four waves share a CU: the softmax
+// takes almost as long as the MFMAs there, and a third wave fills what two
+// leave idle (17,920 tokens x 48 heads, us, against two waves per SIMD, in one
+// workgroup of 256 rows for dense: dense 3804 -> 3619, single pass 4430 -> 4152,
+// block-sparse 20% 914 -> 858, in pairs of blocks of 64 at 10% 680 -> 619).  At
+// d 128 two waves' registers fill the file.
+template <int D>
+constexpr int kWavesPerSimd = D == 64 ? 3 : 2;
+// Waves per workgroup of dense and single-pass attention: 128 query rows at
+// d 64 (three workgroups per CU), 256 at d 128 (one).
+template <int D>
+constexpr int kDenseWaves = D == 64 ? 4 : 8;
+
 template <int D, int NW, bool SPARSE>
-__global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_fwd_kernel(AttnParams a) {
+__global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_fwd_kernel(AttnParams a) {
   attn_fwd_body<D, NW, SPARSE>(a, NoTail{});
 }
 
@@ -570,7 +585,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_fwd_kernel(Attn
 // ragged last block) tiles are done one at a time with key masking.
 // ---------------------------------------------------------------------------
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_sparse_pair_kernel(AttnParams a) {
+__global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_sparse_pair_kernel(AttnParams a) {
   constexpr int NT = 64 * NW;
   constexpr int WPB = NW / 2;        // waves per query block
   constexpr int BLK = 32 * WPB;      // block size: 64 (four waves) or 128 (eight waves)
@@ -826,11 +841,12 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_sparse_pair_ker
         if (n >= PW || (n * SPAN) / PW != slot) return;
         ld.issue_n(n, fill, rKw, rVw, rMw, kbyte, vbyte, mbyte);
       };
+      first_reference(ref, s_cur, sl2, hid);
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
       pipelined_step<D, KS, VS>(loads, sK[RS] + klane, sV[RS] + voff, qf, s_cur, p_prev, s_next, p_cur, o,
                                 sl2, hid ? INFINITY : ref.mc, rsum);
-      move_reference(ref, rsum, bad, s_cur, p_cur, pend, pend_alpha, sl2, c32, hid);
+      move_reference(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32);
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
         s_cur[g] = s_next[g];
@@ -904,11 +920,12 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : 2) void attn_sparse_pair_ker
         if (slot >= PW) return;
         ld.issue_dual_n(slot, fill, rKw, rVw, rMw, ka, kb, va, vb, hmask);
       };
+      first_reference<1>(ref, s_cur, sl2, hid);
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
       pipelined_step<D, KS, VS, 1>(loads, sK[RS] + klane_h, sV[RS] + voff_h, qf, s_cur, p_prev, s_next,
                                    p_cur, o, sl2, hid ? INFINITY : ref.mc, rsum);
-      move_reference<1>(ref, rsum, bad, s_cur, p_cur, pend, pend_alpha, sl2, c32, hid);
+      move_reference<1>(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32);
       s_cur[0] = s_next[0];
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) p_prev[0][s2] = p_cur[0][s2];
@@ -1192,7 +1209,10 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
     wait_vmem();
     __syncthreads();
     f32x16 s_cur[2];
-    if (n_mine > 0) qk_tile<D, KS, G>(sKV[0][sp], qf, c32, hw, s_cur);
+    if (n_mine > 0) {
+      qk_tile<D, KS, G>(sKV[0][sp], qf, c32, hw, s_cur);
+      ref.template raise<G>(s_cur, sl2);
+    }
     __syncthreads();            // slot 0 is refilled by step 0
 
     bf16x8 p_prev[2][2];
@@ -1246,7 +1266,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
       float tsum = 0.f;
       pipelined_step<D, KS, VS, G, BS, true>(hook, rd + klane, rd + LD::VOFF + voff, qf, s_cur, p_prev, s_next,
                                              p_cur, o, sl2, ref.mc, rsum, &tsum);
-      move_reference<G, BS>(ref, rsum, bad, s_cur, p_cur, pend, pend_alpha, sl2, c32, false, &tsum);
+      move_reference<G, BS>(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32, &tsum);
       if constexpr (BS) {
         if (pend) {
           bsum *= pend_alpha;
@@ -1282,7 +1302,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
       }
       pv_tile<ND, VS, G>(sKV[(n_mine - 1) & 1][sp] + LD::VOFF + voff, p_prev, o);
       lsum = finish_sums<G>(rsum, bad, p_prev, hw, c32);
-      bad = bad || !acc_finite<ND>(o);
+      bad = bad || ref.m == -INFINITY || !acc_finite<ND>(o);
       redo = __any(bad);
       if (redo && lane == 0) s_redo = 1;
     }
@@ -1738,8 +1758,9 @@ __global__ __launch_bounds__(512, 1) void fused_search_kernel(AttnParams a, Mass
 // recomputes it in full).
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(512, 1) void single_pass_search_kernel(AttnParams a) {
-  constexpr int NW = 8;
+__global__ __launch_bounds__(64 * kDenseWaves<D>, kDenseWaves<D> >= 8 ? 1 : kWavesPerSimd<D>) void
+single_pass_search_kernel(AttnParams a) {
+  constexpr int NW = kDenseWaves<D>;
   attn_fwd_body<D, NW, false, true>(a, [&](int bh, int qt, const bf16x8 (&)[D / 16], float rowf, float mc,
                                            u16*) {
     const int lane = threadIdx.x & 63;
@@ -1820,6 +1841,19 @@ static hipError_t launch_split(AttnParams a, int D, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Work items of dense and single-pass attention: (head, query tile), without
+// the tiles of the last n_tail 256-row tiles, which run key-split.  At d 128 a
+// workgroup of eight waves takes 256 query rows (every K/V tile brought into
+// LDS serves twice the rows of a 128-row workgroup), at d 64 four waves 128.
+static void plan_dense_items(AttnParams& a, int D) {
+  const int rows = 32 * (D == 64 ? kDenseWaves<64> : kDenseWaves<128>);
+  const int nqt256 = (a.seqlen + 255) / 256, whole = a.batch_heads * nqt256 - a.n_tail;
+  a.nqt = (a.seqlen + rows - 1) / rows;
+  a.n_items = whole / nqt256 * a.nqt + whole % nqt256 * (256 / rows);
+  a.n_wg = a.n_items;
+  if (a.n_items <= 256 * 256 / rows) a.claim = nullptr;      // all run at once: nothing to balance
+}
+
 hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
   a.row_ptr = nullptr;
   a.col_idx = nullptr;
@@ -1828,13 +1862,8 @@ hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
     const hipError_t e = launch_split<false, false>(a, D, st);
     if (e != hipSuccess) return e;
   }
-  // 256 query rows per workgroup (eight waves of 32 rows): every K/V tile
-  // brought into LDS serves twice the rows of a 128-row workgroup.
-  a.nqt = (a.seqlen + 255) / 256;
-  a.n_items = a.nqt * a.batch_heads - a.n_tail;
+  plan_dense_items(a, D);
   if (a.n_items == 0) return hipSuccess;
-  a.n_wg = a.n_items;
-  if (a.n_items <= 256) a.claim = nullptr;      // all run at once: nothing to balance
   if (a.claim != nullptr) {
     // A quarter more workgroups than items: the XCDs that run ahead take the
     // items the others have not reached; surplus workgroups find every queue
@@ -1845,8 +1874,8 @@ hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (D == 64) return launch_attn<64, 8, false>(a, st);
-  return launch_attn<128, 8, false>(a, st);
+  if (D == 64) return launch_attn<64, kDenseWaves<64>, false>(a, st);
+  return launch_attn<128, kDenseWaves<128>, false>(a, st);
 }
 
 // Work items of block-sparse attention: with a workspace, the first nine
@@ -1983,21 +2012,19 @@ hipError_t launch_single_pass_search(AttnParams a, int D, hipStream_t st) {
     const hipError_t e = launch_split<false, true>(a, D, st);
     if (e != hipSuccess) return e;
   }
-  // Work items as in launch_dense: (head, 256-row query tile), two query
-  // blocks of 128 or four of 64.
-  a.nqt = (a.seqlen + 255) / 256;
-  a.n_items = a.split ? 0 : a.nqt * a.batch_heads - a.n_tail;
+  if (a.split) return launch_single_pass_reduce(a, st);
+  plan_dense_items(a, D);
   if (a.n_items == 0) return launch_single_pass_reduce(a, st);
-  a.n_wg = a.n_items;
-  if (a.n_items <= 256) a.claim = nullptr;
   if (a.claim != nullptr) {
     a.n_wg = a.n_items + (a.n_items + 3) / 4;
     hipLaunchKernelGGL(claim_reset_kernel, dim3(1), dim3(64), 0, st, a.claim);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (D == 64) hipLaunchKernelGGL((single_pass_search_kernel<64>), dim3(a.n_wg), dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((single_pass_search_kernel<128>), dim3(a.n_wg), dim3(512), 0, st, a);
+  if (D == 64)
+    hipLaunchKernelGGL((single_pass_search_kernel<64>), dim3(a.n_wg), dim3(64 * kDenseWaves<64>), 0, st, a);
+  else
+    hipLaunchKernelGGL((single_pass_search_kernel<128>), dim3(a.n_wg), dim3(64 * kDenseWaves<128>), 0, st, a);
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_single_pass_reduce(a, st);
 }

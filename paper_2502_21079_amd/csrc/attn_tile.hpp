@@ -353,8 +353,8 @@ __device__ __forceinline__ void zero_lds(u16* p, int tid, int nt) {
 // as exp2(s * sl2 - mc) with mc = m * sl2 for a reference m (raw score units)
 // that is NOT the running maximum, so no per-tile maximum is computed on the
 // common path; the final normalisation uses the same reference, so the
-// result is the softmax whatever the reference.  The first tile with a finite
-// score sets it to that tile's maximum, however negative (against mc = 0 a
+// result is the softmax whatever the reference.  The first tile sets it to
+// that tile's maximum, however negative (against mc = 0 a
 // row whose scaled scores all lie below the fp32 exponent range would sum to
 // zero).  In the pipeline it then moves only when the row's running sum
 // passes kRowSumLimit (move_reference below); on the masked, exact path it
@@ -472,40 +472,56 @@ __device__ __forceinline__ float exp_tile_fsum(const f32x16 (&s)[2], float sl2, 
   return ts;
 }
 
+// Start of a pipelined step of the block-64 pairs (rare branch, taken by the
+// whole wave): rows without a reference yet take the maximum of the tile whose
+// probabilities the step forms (their sums so far are 0).  A tile that only
+// the other query block keeps (hidden) never sets it.
+template <int G = 2>
+__device__ __forceinline__ void first_reference(RowRef& ref, const f32x16 (&s_cur)[2], float sl2, bool hidden) {
+  if (hidden || !__any(ref.m == -INFINITY)) return;
+  RowRef r = ref;
+  r.template raise<G>(s_cur, sl2);
+  if (ref.m == -INFINITY) ref = r;
+}
+
 // End of a pipelined step (rare branch, taken by the whole wave): rows whose
 // running sum (tiles up to the previous one) passed kRowSumLimit move their
-// reference up by log2 of the sum, so the sum becomes about 1; rows without a
-// reference yet take this tile's maximum (their sums so far are 0).  The sums
-// are rescaled here, the output accumulator at the start of the next step
-// (pend), and the current tile's probabilities are taken again against the
-// new reference.  bad is set when a sum has left the safe range.  A hidden
-// tile (block-64 pairs: one the other query block keeps) never sets the
-// reference and its probabilities stay exact zeros.
-// With BS, *tsum receives the fp32 sum of the retaken probabilities.
+// reference up by a whole number of log2 units, about log2 of the sum, so the
+// sum becomes about 1.  What was taken against the old reference scales by
+// an exact power of two: the sums and the current tile's probabilities (and
+// with BS their fp32 sum, *tsum) here, the output accumulator at the start of
+// the next step (pend).  So the tile's scores are not needed any more once
+// its probabilities are taken, and the registers of its two 32-key groups go
+// to the next tile's scores group by group; taking the probabilities again
+// against the new reference kept all of them to the end of every step (dense
+// attention at d 64: 182 registers, now 160).  bad is set when a sum has left
+// the safe range.  A row's first reference is set before the pipeline from its
+// first tile; a row that has none then (no finite score) is redone on the
+// exact path (block-64 pairs, whose first tile may be the other block's, look
+// for it at the start of every step instead).
 template <int G = 2, bool BS = false>
-__device__ __forceinline__ void move_reference(RowRef& ref, RowSums& rsum, bool& bad,
-                                               const f32x16 (&s_cur)[2], bf16x8 (&p_cur)[2][2],
+__device__ __forceinline__ void move_reference(RowRef& ref, RowSums& rsum, bool& bad, bf16x8 (&p_cur)[2][2],
                                                bool& pend, float& pend_alpha, float sl2, int c32,
-                                               bool hidden = false, float* tsum = nullptr) {
+                                               float* tsum = nullptr) {
   const float sr = rsum.acc[0];
-  if (!__any(ref.m == -INFINITY || sr > kRowSumLimit)) return;
+  if (!__any(sr > kRowSumLimit)) return;
   bad = bad || !(sr <= kRowSumBad);
-  const float dr = sr > kRowSumLimit ? __builtin_amdgcn_logf(sr) : 0.f;   // log2 of the sum
+  const float dr = sr > kRowSumLimit ? __builtin_floorf(__builtin_amdgcn_logf(sr)) : 0.f;   // log2 of the sum
   const float ar = fast_exp2(-dr);
 #pragma unroll
   for (int j = 0; j < 4; ++j) rsum.acc[j] *= ar;
   const float d = RowSums::for_row(dr, c32);        // the same value for this lane's row
-  float al;
-  if (ref.m == -INFINITY) {
-    al = hidden ? 1.f : ref.template raise<G>(s_cur, sl2);
-  } else {
-    if (d > 0.f) ref.shift(d, sl2);
-    al = fast_exp2(-d);
-  }
+  const float al = fast_exp2(-d);
+  if (d > 0.f) ref.shift(d, sl2);
   pend_alpha = al;
   pend = true;
-  if constexpr (BS) exp_tile_fsum<G>(s_cur, sl2, hidden ? INFINITY : ref.mc, p_cur, *tsum);
-  else exp_tile<G>(s_cur, sl2, hidden ? INFINITY : ref.mc, p_cur);
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p_cur[g][s2][e] = (__bf16)((float)p_cur[g][s2][e] * al);
+  if constexpr (BS) *tsum *= al;
 }
 
 // After the last pipelined tile: its probabilities join the sums, a sum out
@@ -627,10 +643,11 @@ constexpr int kStageElems = NW * 32 * (D + 8);    // ring elements store_rows us
 
 // One pipelined step, scheduled by hand: NM = 2*NK + 4*ND MFMA slots that
 // alternate a QK MFMA (scores of the next tile) and a PV MFMA (output update
-// of the previous tile).  The QK MFMAs alternate between the two 32-key score
-// groups and the PV MFMAs rotate over the ND output blocks, so two MFMAs into
-// the same accumulator are 4 (QK) or 2*ND (PV) slots apart and one wave alone
-// keeps the matrix pipe busy; each accumulator still sums in the same order.
+// of the previous tile).  The QK MFMAs form one 32-key score group after the
+// other (the current tile's groups are exponentiated in the same order, so a
+// group's registers are free for the next tile's by then) and the PV MFMAs
+// rotate over the ND output blocks, so two MFMAs into the same accumulator
+// are 2 (QK) or 2*ND (PV) slots apart; each accumulator sums in the same order.
 // Each slot first issues the LDS operand reads of the slot LA places ahead,
 // then its MFMA, then hook(slot) (the caller's tile loads, at most one per
 // slot), then its share of the softmax of the current tile against the
@@ -661,8 +678,8 @@ __device__ __forceinline__ void pipelined_step(Hook&& hook, const u16* klane, co
   bf16x8 op[NM];
   auto fetch = [&](int i) {
     const int j = i >> 1;
-    if ((i & 1) == 0) {       // QK j: g = j % G, ks = j / G
-      const int g = j % G, ks = j / G;
+    if ((i & 1) == 0) {       // QK j: g = j / NK, ks = j % NK
+      const int g = j / NK, ks = j % NK;
       op[i] = *reinterpret_cast<const bf16x8*>(klane + (32 * g * KS + 2 * ks) * 8);
     } else {                  // PV j: d = j % ND, (g, s2) = j / ND
       const int d = j % ND, g = (j / ND) >> 1, s2 = (j / ND) & 1;
@@ -676,7 +693,7 @@ __device__ __forceinline__ void pipelined_step(Hook&& hook, const u16* klane, co
   auto mfma = [&](int i) {
     const int j = i >> 1;
     if ((i & 1) == 0) {
-      const int g = j % G, ks = j / G;
+      const int g = j / NK, ks = j % NK;
       if (ks == 0) s_next[g] = mfma32(op[i], qf[ks], f32x16{});
       else s_next[g] = mfma32(op[i], qf[ks], s_next[g]);
     } else {
