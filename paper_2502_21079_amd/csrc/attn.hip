@@ -1819,6 +1819,16 @@ __global__ __launch_bounds__(64 * kReduceWaves) void single_pass_reduce_kernel(A
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Up to this many rounds of workgroups the work queues are left out: an equal
+// share per XCD ends as early there, and the launch that clears the counters
+// and every workgroup's claim cost more than the balance returns (us, with
+// queues and without: dense 9,001 tokens x 12 heads, d 128, 1.7 rounds, 464 and
+// 430; 16,384 x 16, four rounds, 1741 and 1722; but 17,920 x 24, 6.6 rounds,
+// 3130 and 3190; block-sparse 10%, 8,192 x 48, d 64, four rounds, 138 and 123;
+// 9,001 x 12, d 128, 1.7 rounds, 137 and 132, but at four rounds, 16,384 x 16,
+// in pairs of blocks of 64 at 20%, 568 and 585).
+constexpr int kFewRounds = 4;
+
 template <int D, int NW, bool SPARSE>
 static hipError_t launch_attn(const AttnParams& a, hipStream_t st) {
   hipLaunchKernelGGL((attn_fwd_kernel<D, NW, SPARSE>), dim3(a.n_wg), dim3(64 * NW), 0, st, a);
@@ -1851,7 +1861,7 @@ static void plan_dense_items(AttnParams& a, int D) {
   a.nqt = (a.seqlen + rows - 1) / rows;
   a.n_items = whole / nqt256 * a.nqt + whole % nqt256 * (256 / rows);
   a.n_wg = a.n_items;
-  if (a.n_items <= 256 * 256 / rows) a.claim = nullptr;      // all run at once: nothing to balance
+  if (whole <= kFewRounds * 256) a.claim = nullptr;
 }
 
 hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
@@ -1882,10 +1892,12 @@ hipError_t launch_dense(AttnParams a, int D, hipStream_t st) {
 // tenths (rounded down to a multiple of 8) in the static order and the rest
 // claimed from the per-XCD queues, with half as many extra workgroups as
 // queued items (a fast XCD takes up to that many more than its share).
-static hipError_t plan_sparse_items(AttnParams& a, hipStream_t st) {
+static hipError_t plan_sparse_items(AttnParams& a, int D, hipStream_t st) {
   a.n_items = a.nqt * a.batch_heads;
   a.n_static = a.n_items;
   a.n_wg = a.n_items;
+  const int per_round = 256 * (D == 64 ? kWavesPerSimd<64> : kWavesPerSimd<128>);   // four waves each
+  if (a.n_items <= (D == 64 ? kFewRounds : kFewRounds - 1) * per_round) a.claim = nullptr;
   if (a.claim == nullptr) return hipSuccess;
   a.n_static = (int)((int64_t)a.n_items * 9 / 10) / 8 * 8;
   a.n_wg = a.n_items + (a.n_items - a.n_static) / 2;
@@ -1904,7 +1916,6 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
     const hipError_t e = launch_split<true, false>(a, D, st);
     if (e != hipSuccess) return e;
     a.pick = PICK_OTHERS;
-    if (tiles <= 1024) a.claim = nullptr;     // one row per workgroup slot: nothing to balance
   }
   if (a.block == 64) {
     // One workgroup per pair of query blocks (128 rows); text ranges in pairs.
@@ -1914,7 +1925,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
       a.tq1 = (a.tq1 + 1) / 2;
       if (a.tq1 - a.tq0 >= a.nqt) a.tq0 = a.tq1 = 0;
     }
-    const hipError_t e = plan_sparse_items(a, st);
+    const hipError_t e = plan_sparse_items(a, D, st);
     if (e != hipSuccess) return e;
     if (D == 64) hipLaunchKernelGGL((attn_sparse_pair_kernel<64, 4>), dim3(a.n_wg), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((attn_sparse_pair_kernel<128, 4>), dim3(a.n_wg), dim3(256), 0, st, a);
@@ -1922,7 +1933,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   }
   // One workgroup per query block of 128 (four waves).
   a.nqt = a.nkb;
-  const hipError_t e = plan_sparse_items(a, st);
+  const hipError_t e = plan_sparse_items(a, D, st);
   if (e != hipSuccess) return e;
   if (D == 64) return launch_attn<64, 4, true>(a, st);
   return launch_attn<128, 4, true>(a, st);
@@ -1957,7 +1968,7 @@ template <int D, int QB, int NW>
 static hipError_t launch_mass_t(MassParams a, hipStream_t st) {
   plan_mass_items(a, (a.nkb + QB - 1) / QB * a.batch_heads);
   a.n_wg = a.n_items;
-  if (a.n_items <= kMassSlots) a.claim = nullptr;    // all run at once: nothing to balance
+  if (a.n_items <= kFewRounds * kMassSlots) a.claim = nullptr;
   if (a.claim != nullptr) {                  // as in launch_dense
     a.n_wg = a.n_items + (a.n_items + 3) / 4;
     hipLaunchKernelGGL(claim_reset_kernel, dim3(1), dim3(64), 0, st, a.claim);

@@ -66,14 +66,15 @@ inline bool use_key_split(int64_t batch_heads, int seqlen) {
 // whole round, and at d 64 two thirds for up to 128, where a nearly empty
 // round of whole items takes 0.65 (d 128) and 0.77 (d 64) of a full one.  After
 // many rounds the CUs no longer end together and the last items hide among the
-// others' ends, so this stops at five whole rounds.  Dense, us, before and
+// others' ends, so this stops at four whole rounds.  Dense, us, before and
 // after: 8,192 tokens x 9 heads (one round and 32 items) 240 -> 178 at d 64 and
 // 357 -> 291 at d 128; 35,000 x 4 (two and 36) 1492 -> 1282 and 2362 -> 2121;
-// 11,000 x 24 (four and 8) 819 -> 778 and 1284 -> 1276; but 17,920 x 48
-// (thirteen and 32, d 64) 3825 -> 3932.
+// 11,000 x 24 (four and 8) 819 -> 778 and 1284 -> 1276; but
+// 110,336 x 3 (five and 13) gained nothing and 17,920 x 48 (thirteen and 32,
+// d 64) 3825 -> 3932.
 inline int split_tail(int64_t batch_heads, int seqlen, int head_dim) {
   const int64_t n = batch_heads * ((seqlen + 255) / 256), rest = n % 256;
-  if (use_key_split(batch_heads, seqlen) || n < 256 || n / 256 > 5) return 0;
+  if (use_key_split(batch_heads, seqlen) || n < 256 || n / 256 > 4) return 0;
   return rest <= (head_dim == 64 ? 128 : 64) ? (int)rest : 0;
 }
 
