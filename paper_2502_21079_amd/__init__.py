@@ -19,6 +19,7 @@ There is no CPU fallback: if the library is missing, every call raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 from typing import Optional, Sequence
@@ -127,29 +128,41 @@ def _check(status: int):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# The current stream's handle without building a torch.cuda.Stream object for
+# it (a microsecond or two of a call that may take ten).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _problem(q: torch.Tensor, block: int, text_start: int, text_len: int,
-             scale: Optional[float]) -> _Problem:
-    B, H, L, D = q.shape
-    return _Problem(B, H, L, D, block, text_start, text_len,
-                    0.0 if scale is None else float(scale))
+def _stream(device):
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+# The argument structures of a call are made once per set of values (sizes and
+# parameters, never tensors) and only read from then on, by the library too.
+@functools.lru_cache(maxsize=256, typed=True)
+def _problem_ref(B, H, L, D, block, text_start, text_len, scale):
+    return ctypes.byref(_Problem(B, H, L, D, block, text_start, text_len, scale))
+
+
+def _problem(shape, block: int, text_start: int, text_len: int, scale: Optional[float]):
+    return _problem_ref(*shape, block, text_start, text_len, 0.0 if scale is None else float(scale))
 
 
 def _check_qkv(*ts):
     ref = ts[0]
+    shape = ref.shape
     for t in ts:
         if t is None:
             continue
-        if t.dtype != torch.bfloat16 or t.device.type != "cuda" or not t.is_contiguous():
+        if t.dtype is not torch.bfloat16 or not t.is_cuda or not t.is_contiguous():
             raise AdaspaError("q, k, v must be contiguous bf16 CUDA tensors [B, H, L, D]")
-        if t.shape != ref.shape:
-            raise AdaspaError(f"shape mismatch {tuple(t.shape)} vs {tuple(ref.shape)}")
+        if t is not ref and t.shape != shape:
+            raise AdaspaError(f"shape mismatch {tuple(t.shape)} vs {tuple(shape)}")
 
 
 def _check_outputs(q, out, lse):
@@ -174,22 +187,35 @@ def _workspace_bytes(workspace, dev) -> int:
     return workspace.numel() * workspace.element_size()
 
 
-def _select(mode: str, head_param_bp: Optional[Sequence[int]], text_sink: bool,
-            scores_given: bool, base_sparsity_bp: int = 8000, recall_threshold_bp: int = 8000,
-            heads: Optional[int] = None):
-    modes = {"topk": SELECT_TOPK, "coverage": SELECT_COVERAGE, "hierarchical": SELECT_HIERARCHICAL}
-    if mode not in modes:
+def _search_args(shape, block, text_start, text_len, scale, mode, head_param_bp, text_sink, scores_given,
+                 base_sparsity_bp: int = 8000, recall_threshold_bp: int = 8000):
+    """(problem, selection, capacity, workspace bytes) of a search's arguments."""
+    if mode not in _MODES:
         raise AdaspaError(f"unknown selection mode {mode!r}")
-    m = modes[mode]
-    params = list(head_param_bp) if head_param_bp is not None else []
+    params = tuple([int(x) for x in head_param_bp]) if head_param_bp is not None else ()
     # The library reads head_param_bp[0 .. H-1] in the per-head modes: a shorter
     # list would be read past its end.
-    if m != SELECT_HIERARCHICAL and heads is not None and len(params) != heads:
-        raise AdaspaError(f"head_param_bp needs one entry per head ({heads}), got {len(params)}")
-    arr = (ctypes.c_int32 * max(1, len(params)))(*[int(x) for x in params])
-    ptr = ctypes.cast(arr, ctypes.POINTER(ctypes.c_int32)) if params else None
+    if mode != "hierarchical" and len(params) != shape[1]:
+        raise AdaspaError(f"head_param_bp needs one entry per head ({shape[1]}), got {len(params)}")
     flags = (F_TEXT_SINK if text_sink else 0) | (F_SCORES_GIVEN if scores_given else 0)
-    return _Select(m, flags, ptr, int(base_sparsity_bp), int(recall_threshold_bp)), arr
+    return _search_plan(*shape, block, text_start, text_len, 0.0 if scale is None else float(scale),
+                        _MODES[mode], flags, params, int(base_sparsity_bp), int(recall_threshold_bp))
+
+
+_MODES = {"topk": SELECT_TOPK, "coverage": SELECT_COVERAGE, "hierarchical": SELECT_HIERARCHICAL}
+
+
+@functools.lru_cache(maxsize=256, typed=True)
+def _search_plan(B, H, L, D, block, text_start, text_len, scale, mode, flags, params, base_sparsity_bp,
+                 recall_threshold_bp):
+    lib = load_library()
+    arr = (ctypes.c_int32 * max(1, len(params)))(*params)
+    sel = _Select(mode, flags, ctypes.cast(arr, ctypes.POINTER(ctypes.c_int32)) if params else None,
+                  base_sparsity_bp, recall_threshold_bp)
+    sel._params = arr                     # lives as long as the structure that points to it
+    prob, ref = _problem_ref(B, H, L, D, block, text_start, text_len, scale), ctypes.byref(sel)
+    return (prob, ref, int(lib.adaspa_block_search_capacity(prob, ref)),
+            int(lib.adaspa_block_search_workspace(prob, ref)))
 
 
 def dense_attn_lse(q, k, v, *, scale: Optional[float] = None, out=None, lse=None,
@@ -209,26 +235,22 @@ def dense_attn_lse(q, k, v, *, scale: Optional[float] = None, out=None, lse=None
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(B, H, L, dtype=torch.float32, device=q.device)
-    prob = _problem(q, 128, 0, 0, scale)
+    prob = _problem(q.shape, 128, 0, 0, scale)
     ws_bytes = 0
     if balance:
-        ws_bytes = int(lib.adaspa_dense_attn_workspace(ctypes.byref(prob)))
         if workspace is None:
-            workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
+            workspace = torch.empty(lib.adaspa_dense_attn_workspace(prob), dtype=torch.uint8, device=q.device)
         ws_bytes = _workspace_bytes(workspace, q.device)
     else:
         workspace = None
-    _check(lib.adaspa_dense_attn_lse(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                     _ptr(lse), _ptr(workspace), ctypes.c_size_t(ws_bytes),
-                                     _stream(q.device)))
+    _check(lib.adaspa_dense_attn_lse(prob, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(workspace),
+                                     ws_bytes, _stream(q.device)))
     return out, lse
 
 
 def dense_attn_workspace(shape, scale: Optional[float] = None) -> int:
     """Bytes of the work-queue workspace of :func:`dense_attn_lse`."""
-    B, H, L, D = shape
-    prob = _Problem(B, H, L, D, 128, 0, 0, 0.0 if scale is None else float(scale))
-    return int(load_library().adaspa_dense_attn_workspace(ctypes.byref(prob)))
+    return int(load_library().adaspa_dense_attn_workspace(_problem(shape, 128, 0, 0, scale)))
 
 
 @dataclass
@@ -243,24 +265,14 @@ class SearchResult:
         return int(self.row_ptr[-1].item())
 
 
-def _problem_shape(B, H, L, D, block, text_start, text_len, scale):
-    return _Problem(B, H, L, D, block, text_start, text_len, 0.0 if scale is None else float(scale))
-
-
 def block_search_workspace(shape, block, text_start, text_len, mode, head_param_bp,
                            text_sink=True) -> int:
-    B, H, L, D = shape
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, None)
-    sel, _keep = _select(mode, head_param_bp, text_sink, False, heads=H)
-    return int(load_library().adaspa_block_search_workspace(ctypes.byref(prob), ctypes.byref(sel)))
+    return _search_args(shape, block, text_start, text_len, None, mode, head_param_bp, text_sink, False)[3]
 
 
 def block_search_capacity(shape, block, text_start, text_len, mode, head_param_bp,
                           text_sink=True) -> int:
-    B, H, L, D = shape
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, None)
-    sel, _keep = _select(mode, head_param_bp, text_sink, False, heads=H)
-    return int(load_library().adaspa_block_search_capacity(ctypes.byref(prob), ctypes.byref(sel)))
+    return _search_args(shape, block, text_start, text_len, None, mode, head_param_bp, text_sink, False)[2]
 
 
 def block_search(q, k, lse, *, block: int, text_start: int, text_len: int,
@@ -288,20 +300,17 @@ def block_search(q, k, lse, *, block: int, text_start: int, text_len: int,
         if lse.dtype != torch.float32 or not lse.is_contiguous() or lse.shape != (B, H, L):
             raise AdaspaError("lse must be contiguous fp32 [B, H, L]")
     nb = (L + block - 1) // block
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, scale)
-    sel, _keep = _select(mode, head_param_bp, text_sink, given, base_sparsity_bp,
-                         recall_threshold_bp, heads=H)
-    cap = lib.adaspa_block_search_capacity(ctypes.byref(prob), ctypes.byref(sel))
-    wsb = lib.adaspa_block_search_workspace(ctypes.byref(prob), ctypes.byref(sel))
+    prob, sel, cap, wsb = _search_args((B, H, L, D), block, text_start, text_len, scale, mode, head_param_bp,
+                                       text_sink, given, base_sparsity_bp, recall_threshold_bp)
     if cap < 0 or wsb == 0:
-        _check(lib.adaspa_block_search(ctypes.byref(prob), None, None, None, ctypes.byref(sel),
+        _check(lib.adaspa_block_search(prob, None, None, None, sel,
                                        None, None, None, 0, None, None, None, 0, None))
         raise AdaspaError("invalid block_search arguments")
     res = _search_outputs(B, H, nb, cap, dev, result, scores)
     if workspace is None or _workspace_bytes(workspace, dev) < wsb:
         workspace = torch.empty(int(wsb), dtype=torch.uint8, device=dev)
-    _check(lib.adaspa_block_search(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(lse),
-                                   ctypes.byref(sel), _ptr(res.block_mass), _ptr(res.row_ptr),
+    _check(lib.adaspa_block_search(prob, _ptr(q), _ptr(k), _ptr(lse),
+                                   sel, _ptr(res.block_mass), _ptr(res.row_ptr),
                                    _ptr(res.col_idx), int(res.col_idx.numel()), _ptr(res.head_k),
                                    _ptr(res.head_recall), _ptr(workspace), _workspace_bytes(workspace, dev),
                                    _stream(dev)))
@@ -346,14 +355,11 @@ def fused_online_search(q, k, v, *, block: int, text_start: int, text_len: int, 
     B, H, L, D = q.shape
     dev = q.device
     nb = (L + block - 1) // block
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, scale)
-    sel, _keep = _select(mode, head_param_bp, text_sink, False, base_sparsity_bp,
-                         recall_threshold_bp, heads=H)
-    cap = lib.adaspa_block_search_capacity(ctypes.byref(prob), ctypes.byref(sel))
-    wsb = lib.adaspa_block_search_workspace(ctypes.byref(prob), ctypes.byref(sel))
+    prob, sel, cap, wsb = _search_args((B, H, L, D), block, text_start, text_len, scale, mode, head_param_bp,
+                                       text_sink, False, base_sparsity_bp, recall_threshold_bp)
     if cap < 0 or wsb == 0:
-        _check(lib.adaspa_fused_online_search(ctypes.byref(prob), None, None, None, None, None,
-                                              ctypes.byref(sel), None, None, None, 0, None, None,
+        _check(lib.adaspa_fused_online_search(prob, None, None, None, None, None,
+                                              sel, None, None, None, 0, None, None,
                                               None, 0, None))
         raise AdaspaError("invalid fused_online_search arguments")
     _check_outputs(q, out, lse)
@@ -364,8 +370,8 @@ def fused_online_search(q, k, v, *, block: int, text_start: int, text_len: int, 
     res = _search_outputs(B, H, nb, cap, dev, result)
     if workspace is None or _workspace_bytes(workspace, dev) < wsb:
         workspace = torch.empty(int(wsb), dtype=torch.uint8, device=dev)
-    _check(lib.adaspa_fused_online_search(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                          _ptr(lse), ctypes.byref(sel), _ptr(res.block_mass),
+    _check(lib.adaspa_fused_online_search(prob, _ptr(q), _ptr(k), _ptr(v), _ptr(out),
+                                          _ptr(lse), sel, _ptr(res.block_mass),
                                           _ptr(res.row_ptr), _ptr(res.col_idx),
                                           int(res.col_idx.numel()), _ptr(res.head_k),
                                           _ptr(res.head_recall), _ptr(workspace),
@@ -378,12 +384,9 @@ def single_pass_online_search_workspace(shape, block, text_start, text_len, mode
                                         recall_threshold_bp: int = 8000) -> int:
     """Bytes of the workspace of :func:`single_pass_online_search`: the
     search's scratch plus B*H*NB*L floats of per-row block masses."""
-    B, H, L, D = shape
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, None)
-    sel, _keep = _select(mode, head_param_bp, text_sink, False, base_sparsity_bp, recall_threshold_bp,
-                         heads=H)
-    return int(load_library().adaspa_single_pass_online_search_workspace(ctypes.byref(prob),
-                                                                         ctypes.byref(sel)))
+    prob, sel, _, _ = _search_args(shape, block, text_start, text_len, None, mode, head_param_bp, text_sink, False,
+                                   base_sparsity_bp, recall_threshold_bp)
+    return int(load_library().adaspa_single_pass_online_search_workspace(prob, sel))
 
 
 def single_pass_online_search_min_workspace(shape, block, text_start, text_len, mode, head_param_bp=None,
@@ -392,12 +395,9 @@ def single_pass_online_search_min_workspace(shape, block, text_start, text_len, 
     """The least workspace :func:`single_pass_online_search` accepts (one
     (batch, head) pair's per-row block masses); with less than the full size
     the call runs the (batch, head) pairs in groups, with the same results."""
-    B, H, L, D = shape
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, None)
-    sel, _keep = _select(mode, head_param_bp, text_sink, False, base_sparsity_bp, recall_threshold_bp,
-                         heads=H)
-    return int(load_library().adaspa_single_pass_online_search_min_workspace(ctypes.byref(prob),
-                                                                             ctypes.byref(sel)))
+    prob, sel, _, _ = _search_args(shape, block, text_start, text_len, None, mode, head_param_bp, text_sink, False,
+                                   base_sparsity_bp, recall_threshold_bp)
+    return int(load_library().adaspa_single_pass_online_search_min_workspace(prob, sel))
 
 
 def single_pass_online_search(q, k, v, *, block: int, text_start: int, text_len: int, mode: str,
@@ -422,15 +422,13 @@ def single_pass_online_search(q, k, v, *, block: int, text_start: int, text_len:
     B, H, L, D = q.shape
     dev = q.device
     nb = (L + block - 1) // block
-    prob = _problem_shape(B, H, L, D, block, text_start, text_len, scale)
-    sel, _keep = _select(mode, head_param_bp, text_sink, False, base_sparsity_bp,
-                         recall_threshold_bp, heads=H)
-    cap = lib.adaspa_block_search_capacity(ctypes.byref(prob), ctypes.byref(sel))
-    wsb = lib.adaspa_single_pass_online_search_workspace(ctypes.byref(prob), ctypes.byref(sel))
-    wsb_min = lib.adaspa_single_pass_online_search_min_workspace(ctypes.byref(prob), ctypes.byref(sel))
+    prob, sel, cap, _ = _search_args((B, H, L, D), block, text_start, text_len, scale, mode, head_param_bp,
+                                     text_sink, False, base_sparsity_bp, recall_threshold_bp)
+    wsb = lib.adaspa_single_pass_online_search_workspace(prob, sel)
+    wsb_min = lib.adaspa_single_pass_online_search_min_workspace(prob, sel)
     if cap < 0 or wsb == 0:
-        _check(lib.adaspa_single_pass_online_search(ctypes.byref(prob), None, None, None, None, None,
-                                                    ctypes.byref(sel), None, None, None, 0, None, None,
+        _check(lib.adaspa_single_pass_online_search(prob, None, None, None, None, None,
+                                                    sel, None, None, None, 0, None, None,
                                                     None, 0, None))
         raise AdaspaError("invalid single_pass_online_search arguments")
     _check_outputs(q, out, lse)
@@ -441,8 +439,8 @@ def single_pass_online_search(q, k, v, *, block: int, text_start: int, text_len:
     res = _search_outputs(B, H, nb, cap, dev, result)
     if workspace is None or _workspace_bytes(workspace, dev) < wsb_min:
         workspace = torch.empty(int(wsb), dtype=torch.uint8, device=dev)
-    _check(lib.adaspa_single_pass_online_search(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                                _ptr(lse), ctypes.byref(sel), _ptr(res.block_mass),
+    _check(lib.adaspa_single_pass_online_search(prob, _ptr(q), _ptr(k), _ptr(v), _ptr(out),
+                                                _ptr(lse), sel, _ptr(res.block_mass),
                                                 _ptr(res.row_ptr), _ptr(res.col_idx),
                                                 int(res.col_idx.numel()), _ptr(res.head_k),
                                                 _ptr(res.head_recall), _ptr(workspace),
@@ -475,27 +473,25 @@ def block_sparse_attn(q, k, v, row_ptr, col_idx, *, block: int, scale: Optional[
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(B, H, L, dtype=torch.float32, device=q.device)
-    prob = _problem(q, block, text_start, text_len, scale)
+    prob = _problem(q.shape, block, text_start, text_len, scale)
     ws_bytes = 0
     if balance:
-        ws_bytes = int(lib.adaspa_block_sparse_attn_workspace(ctypes.byref(prob)))
         if workspace is None:
-            workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
+            workspace = torch.empty(lib.adaspa_block_sparse_attn_workspace(prob), dtype=torch.uint8,
+                                    device=q.device)
         ws_bytes = _workspace_bytes(workspace, q.device)
     else:
         workspace = None
-    _check(lib.adaspa_block_sparse_attn(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(v),
+    _check(lib.adaspa_block_sparse_attn(prob, _ptr(q), _ptr(k), _ptr(v),
                                         _ptr(row_ptr), _ptr(col_idx), int(col_idx.numel()),
                                         _ptr(out), _ptr(lse), _ptr(workspace),
-                                        ctypes.c_size_t(ws_bytes), _stream(q.device)))
+                                        ws_bytes, _stream(q.device)))
     return out, lse
 
 
 def block_sparse_attn_workspace(shape, block: int = 128, scale: Optional[float] = None) -> int:
     """Bytes of the work-queue workspace of :func:`block_sparse_attn`."""
-    B, H, L, D = shape
-    prob = _Problem(B, H, L, D, block, 0, 0, 0.0 if scale is None else float(scale))
-    return int(load_library().adaspa_block_sparse_attn_workspace(ctypes.byref(prob)))
+    return int(load_library().adaspa_block_sparse_attn_workspace(_problem(shape, block, 0, 0, scale)))
 
 
 def block_sparse_attn_noalloc(q, k, v, row_ptr, col_idx, *, block: int, out, lse=None,
@@ -517,8 +513,8 @@ def block_sparse_attn_noalloc(q, k, v, row_ptr, col_idx, *, block: int, out, lse
     if row_ptr.numel() != B * H * nb + 1:
         raise AdaspaError(f"row_ptr must have B*H*NB+1 = {B * H * nb + 1} entries")
     _check_outputs(q, out, lse)
-    prob = _problem(q, block, text_start, text_len, scale)
-    _check(lib.adaspa_block_sparse_attn_noalloc(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(v),
+    prob = _problem(q.shape, block, text_start, text_len, scale)
+    _check(lib.adaspa_block_sparse_attn_noalloc(prob, _ptr(q), _ptr(k), _ptr(v),
                                                 _ptr(row_ptr), _ptr(col_idx), int(col_idx.numel()),
                                                 _ptr(out), _ptr(lse), _stream(q.device)))
     return out, lse
