@@ -107,9 +107,8 @@ template <int D, int NW, bool SPARSE, bool BS = false, typename Tail>
 __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   static_assert(!(SPARSE && BS), "block masses come from the dense pass");
   constexpr int NT = 64 * NW;
-  using KDMA = TileDMA<D, NW, 1>;
-  using VDMA = TileDMA<D, NW, 2>;
-  constexpr int KS = KDMA::S, VS = VDMA::S;
+  using KDMA = TileDMA<D, NW, K_TILE>;
+  using VDMA = TileDMA<D, NW, V_TILE>;
   constexpr int ND = D / 32;   // 32-wide output column blocks
   constexpr int NK = D / 16;   // MFMA k-steps over the head dimension
   // A ring of two slots, each [K tile | V tile]; step t reads K(t+1) and
@@ -163,8 +162,8 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   const __amdgpu_buffer_rsrc_t rV = make_rsrc(a.v + hoff, hbytes);
   const u32x4 rKw = rsrc_words(a.k + hoff, hbytes), rVw = rsrc_words(a.v + hoff, hbytes);
   const int qrow = qt * (32 * NW) + wave * 32 + c32;
-  const int voff = ((4 * hw + (gi >> 2)) * VS) * 8 + 16 * (grp & 1) + 4 * (gi & 3);
-  const int klane = (c32 * KS + hw) * 8;
+  const int voff = v_lane<D>(gi, grp, hw);
+  const int klane = k_lane<D>(c32, hw);
 
   // V slots hold finite values whatever a bounds-checked load leaves behind
   // (a key masked to -inf still multiplies its V row by a zero probability);
@@ -319,7 +318,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
     wait_vmem();
     __syncthreads();
     f32x16 s_cur[2];
-    qk_tile<D, KS>(sK[0], qf, c32, hw, s_cur);
+    qk_tile<D>(sK[0], klane, qf, s_cur);
     ref.raise(s_cur, sl2);      // the rows' first reference
     __syncthreads();            // slot 0 is refilled by step 0
 
@@ -336,7 +335,6 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
 
     LD ld;
     ld.init(wave, lane);
-    const u32x4 rMw = ld.mixed_v ? rVw : rKw;     // resource of this wave's mixed entry
 
     // Step t reads K(t+1) and V(t-1) from slot (t+1)&1 and loads K(t+2) and
     // V(t) into slot t&1, which step t-1 read: a slot is refilled only after
@@ -376,7 +374,6 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
       // the loop (which overflows the scalar registers).
       uint32_t fill = lds_addr(sKV[t & 1]);
       asm volatile("" : "+s"(fill));
-      const uint32_t mbyte = ld.mixed_v ? vbyte : kbyte;
       auto loads = [&](int slot) {
         // Load n goes to slot n * SPAN / PW (at most one per slot): the
         // loads fill the first 5/16 of the step, so the last of them has
@@ -385,7 +382,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
         static_assert(PW <= SPAN, "one load instruction per slot at most");
         const int n = (slot * PW + SPAN - 1) / SPAN;
         if (n >= PW || (n * SPAN) / PW != slot) return;
-        ld.issue_n(n, fill, rKw, rVw, rMw, kbyte, vbyte, mbyte);
+        ld.issue_n(n, fill, rKw, rVw, kbyte, vbyte);
       };
       auto hook = [&](int slot) {
         loads(slot);
@@ -395,7 +392,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
       float tsum = 0.f;
-      pipelined_step<D, KS, VS, 2, BS, !SPARSE>(hook, rdK + klane, rdV + voff, qf, s_cur, p_prev, s_next, p_cur, o,
+      pipelined_step<D, 2, BS, !SPARSE>(hook, rdK, klane, rdV, voff, qf, s_cur, p_prev, s_next, p_cur, o,
                                        sl2, ref.mc, rsum, &tsum);
       move_reference<2, BS>(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32, &tsum);
       if constexpr (BS) {
@@ -435,7 +432,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[d][e] *= pend_alpha;
     }
-    pv_tile<ND, VS>(sV[(nf - 1) & (RING - 1)] + voff, p_prev, o);
+    pv_tile<ND>(sV[(nf - 1) & (RING - 1)], voff, p_prev, o);
     lsum = finish_sums(rsum, bad, p_prev, hw, c32);
     bad = bad || ref.m == -INFINITY || !acc_finite<ND>(o);
     redo = __any(bad);
@@ -462,7 +459,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
     __syncthreads();
     if (compute) {
       f32x16 s[2];
-      qk_tile<D, KS>(sK[0], qf, c32, hw, s);
+      qk_tile<D>(sK[0], klane, qf, s);
       mask_tile(s, L - kb, hw);
       bf16x8 pb[2][2];
       float alpha;
@@ -478,7 +475,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
       for (int d = 0; d < ND; ++d)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[d][e] *= alpha;
-      pv_tile<ND, VS>(sV[0] + voff, pb, o);
+      pv_tile<ND>(sV[0], voff, pb, o);
     }
     __syncthreads();
   };
@@ -524,7 +521,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   // Every wave's tile loads have landed and its reads of the ring are done.
   static_assert(kStageElems<D, NW> <= RING * LD::ELEMS, "the output tiles fit the ring");
   __syncthreads();
-  store_rows<D>(o, inv, &sKV[0][0] + wave * 32 * (D + 8), a.o + hoff, qt * (32 * NW) + wave * 32, L, lane);
+  store_rows<D>(o, inv, &sKV[0][0] + wave * 32 * D, a.o + hoff, qt * (32 * NW) + wave * 32, L, lane);
   if (qrow < L && hw == 0 && a.lse != nullptr)
     a.lse[(size_t)bh * L + qrow] = lt > 0.f ? fmaf(ref.m, a.scale, logf(lt)) : -INFINITY;
   // The row's Q fragments, its sum and reference (LSE = m * scale + log lt)
@@ -590,9 +587,8 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
   constexpr int WPB = NW / 2;        // waves per query block
   constexpr int BLK = 32 * WPB;      // block size: 64 (four waves) or 128 (eight waves)
   constexpr int SUB = BLK / KT;      // 64-key tiles per block
-  using KDMA = TileDMA<D, NW, 1>;
-  using VDMA = TileDMA<D, NW, 2>;
-  constexpr int KS = KDMA::S, VS = VDMA::S;
+  using KDMA = TileDMA<D, NW, K_TILE>;
+  using VDMA = TileDMA<D, NW, V_TILE>;
   constexpr int ND = D / 32;
   constexpr int NK = D / 16;
   using LD = KVLoader<D, NW>;
@@ -626,8 +622,8 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
   const __amdgpu_buffer_rsrc_t rV = make_rsrc(a.v + hoff, hbytes);
   const u32x4 rKw = rsrc_words(a.k + hoff, hbytes), rVw = rsrc_words(a.v + hoff, hbytes);
   const int qrow = pq * (2 * BLK) + wave * 32 + c32;
-  const int voff = ((4 * hw + (gi >> 2)) * VS) * 8 + 16 * (grp & 1) + 4 * (gi & 3);
-  const int klane = (c32 * KS + hw) * 8;
+  const int voff = v_lane<D>(gi, grp, hw);
+  const int klane = k_lane<D>(c32, hw);
 
 #pragma unroll
   for (int b = 0; b < 2; ++b) zero_lds<VDMA::SLOTS>(sV[b], tid, NT);   // finite V
@@ -787,7 +783,6 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
   bool bad = false;
   LD ld;
   ld.init(wave, lane);
-  const u32x4 rMw = ld.mixed_v ? rVw : rKw;     // resource of this wave's mixed entry
   auto rescale_pending = [&]() {
     if (pend) {             // the reference moved at the previous step
 #pragma unroll
@@ -817,7 +812,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
     wait_vmem();
     __syncthreads();
     f32x16 s_cur[2];
-    qk_tile<D, KS>(sK[0], qf, c32, hw, s_cur);
+    qk_tile<D>(sK[0], klane, qf, s_cur);
     bool hid = !(uk[0] & mybit);
     __syncthreads();                  // sK[0] is refilled by step 0
 #pragma unroll
@@ -833,18 +828,17 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
       asm volatile("" : "+s"(kbyte), "+s"(vbyte));
       uint32_t fill = lds_addr(sKV[1 - RS]);
       asm volatile("" : "+s"(fill));
-      const uint32_t mbyte = ld.mixed_v ? vbyte : kbyte;
       auto loads = [&](int slot) {
         constexpr int PW = LD::PW, SPAN = (2 * NK + 4 * ND) * 5 / 16;   // as in attn_fwd_kernel
         static_assert(PW <= SPAN, "one load instruction per slot at most");
         const int n = (slot * PW + SPAN - 1) / SPAN;
         if (n >= PW || (n * SPAN) / PW != slot) return;
-        ld.issue_n(n, fill, rKw, rVw, rMw, kbyte, vbyte, mbyte);
+        ld.issue_n(n, fill, rKw, rVw, kbyte, vbyte);
       };
       first_reference(ref, s_cur, sl2, hid);
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
-      pipelined_step<D, KS, VS>(loads, sK[RS] + klane, sV[RS] + voff, qf, s_cur, p_prev, s_next, p_cur, o,
+      pipelined_step<D>(loads, sK[RS], klane, sV[RS], voff, qf, s_cur, p_prev, s_next, p_cur, o,
                                 sl2, hid ? INFINITY : ref.mc, rsum);
       move_reference(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32);
 #pragma unroll
@@ -870,7 +864,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
     }
     if (t < nf1) step(t, std::integral_constant<int, 1>{});
     rescale_pending();
-    pv_tile<ND, VS>(sV[(nf1 - 1) & 1] + voff, p_prev, o);
+    pv_tile<ND>(sV[(nf1 - 1) & 1], voff, p_prev, o);
 #pragma unroll
     for (int j = 0; j < 4; ++j) rsum.add(p_prev[j >> 1][j & 1]);
     bad = bad || !(rsum.acc[0] <= kRowSumBad);
@@ -890,15 +884,13 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
     qb[0] = next_of(sb, 2, kp);
     qb[1] = next_of(sb, 2, kp);
     auto key = [](int t, int n, int blk) { return t < n ? blk * BLK + 32 * (t & 1) : 0; };
-    TileDMA<D, NW, 1>::issue_dual(rK, sK[0], key(0, nA2, qa[0]), key(0, nB2, qb[0]), wave, lane);
-    TileDMA<D, NW, 1>::issue_dual(rK, sK[1], key(1, nA2, qa[0]), key(1, nB2, qb[0]), wave, lane);
+    TileDMA<D, NW, K_TILE>::issue_dual(rK, sK[0], key(0, nA2, qa[0]), key(0, nB2, qb[0]), wave, lane);
+    TileDMA<D, NW, K_TILE>::issue_dual(rK, sK[1], key(1, nA2, qa[0]), key(1, nB2, qb[0]), wave, lane);
     wait_vmem();
     __syncthreads();
-    const int klane_h = klane + half * 32 * KS * 8;
-    const int voff_h = voff + half * 32 * VS * 8;
-    const uint32_t hmask = LD::half_mask(wave, lane);
+    const int half_rows = half * 32 * D;      // this half's rows of a tile
     f32x16 s_cur[2];
-    qk_tile<D, KS, 1>(sK[0] + klane_h - klane, qf, c32, hw, s_cur);
+    qk_tile<D, 1>(sK[0] + half_rows, klane, qf, s_cur);
     bool hid = 0 >= n_mine;
     __syncthreads();                  // sK[0] is refilled by step 0
 #pragma unroll
@@ -907,23 +899,22 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
     auto step2 = [&](int t, auto rs_c) {
       constexpr int RS = decltype(rs_c)::value;
       rescale_pending();
-      constexpr uint32_t HALF_BYTES = 32u * D * 2u;
       uint32_t ka = (uint32_t)key(t + 2, nA2, qa[1]) * (uint32_t)(D * 2);
-      uint32_t kb = (uint32_t)key(t + 2, nB2, qb[1]) * (uint32_t)(D * 2) - HALF_BYTES;
+      uint32_t kb = (uint32_t)key(t + 2, nB2, qb[1]) * (uint32_t)(D * 2);
       uint32_t va = (uint32_t)key(t, nA2, qa[0]) * (uint32_t)(D * 2);
-      uint32_t vb = (uint32_t)key(t, nB2, qb[0]) * (uint32_t)(D * 2) - HALF_BYTES;
+      uint32_t vb = (uint32_t)key(t, nB2, qb[0]) * (uint32_t)(D * 2);
       asm volatile("" : "+s"(ka), "+s"(kb), "+s"(va), "+s"(vb));
       uint32_t fill = lds_addr(sKV[1 - RS]);
       asm volatile("" : "+s"(fill));
       auto loads = [&](int slot) {      // loads in the first PW slots of the step
         constexpr int PW = LD::PW;
         if (slot >= PW) return;
-        ld.issue_dual_n(slot, fill, rKw, rVw, rMw, ka, kb, va, vb, hmask);
+        ld.issue_dual_n(slot, fill, rKw, rVw, ka, kb, va, vb);
       };
       first_reference<1>(ref, s_cur, sl2, hid);
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
-      pipelined_step<D, KS, VS, 1>(loads, sK[RS] + klane_h, sV[RS] + voff_h, qf, s_cur, p_prev, s_next,
+      pipelined_step<D, 1>(loads, sK[RS] + half_rows, klane, sV[RS] + half_rows, voff, qf, s_cur, p_prev, s_next,
                                    p_cur, o, sl2, hid ? INFINITY : ref.mc, rsum);
       move_reference<1>(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32);
       s_cur[0] = s_next[0];
@@ -946,7 +937,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
     }
     if (t < nf2) step2(t, std::integral_constant<int, 1>{});
     rescale_pending();
-    pv_tile<ND, VS, 1>(sV[(nf2 - 1) & 1] + voff_h, p_prev, o);
+    pv_tile<ND, 1>(sV[(nf2 - 1) & 1] + half_rows, voff, p_prev, o);
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) rsum.add(p_prev[0][s2]);
     bad = bad || !(rsum.acc[0] <= kRowSumBad);
@@ -977,7 +968,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
     __syncthreads();
     if (compute) {
       f32x16 s[2];
-      qk_tile<D, KS>(sK[0], qf, c32, hw, s);
+      qk_tile<D>(sK[0], klane, qf, s);
       mask_tile(s, L - kb, hw);
       if (!(keep & mybit)) hide(s);
       bf16x8 pb[2][2];
@@ -986,7 +977,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
       for (int d = 0; d < ND; ++d)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[d][e] *= alpha;
-      pv_tile<ND, VS>(sV[0] + voff, pb, o);
+      pv_tile<ND>(sV[0], voff, pb, o);
     }
     __syncthreads();
   };
@@ -1018,7 +1009,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
   // As in attn_fwd_body: the output tiles go out through the free ring.
   static_assert(kStageElems<D, NW> <= 2 * LD::ELEMS, "the output tiles fit the ring");
   __syncthreads();
-  store_rows<D>(o, inv, &sKV[0][0] + wave * 32 * (D + 8), a.o + hoff, pq * (2 * BLK) + wave * 32, L, lane);
+  store_rows<D>(o, inv, &sKV[0][0] + wave * 32 * D, a.o + hoff, pq * (2 * BLK) + wave * 32, L, lane);
   if (qrow < L && hw == 0 && a.lse != nullptr)
     a.lse[(size_t)bh * L + qrow] = lt > 0.f ? fmaf(ref.m, a.scale, logf(lt)) : -INFINITY;
 }
@@ -1058,7 +1049,6 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
   using LD = KVLoader<D, RG, KEYS>;
   using KDMA = typename LD::K;
   using VDMA = typename LD::V;
-  constexpr int KS = KDMA::S, VS = VDMA::S;
   constexpr int ND = D / 32, NK = D / 16;
   __shared__ __attribute__((aligned(1024))) u16 sKV[2][NS][LD::ELEMS];   // ring slots of [K | V] tiles
   __shared__ float sStat[4][NS][kSplitRows];               // partial references, sums
@@ -1094,8 +1084,8 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
   const u32x4 rKw = rsrc_words(a.k + hoff, hbytes), rVw = rsrc_words(a.v + hoff, hbytes);
   const int row0 = qt * kSplitRows;
   const int qrow = row0 + rg * 32 + c32;
-  const int voff = ((4 * hw + (gi >> 2)) * VS) * 8 + 16 * (grp & 1) + 4 * (gi & 3);
-  const int klane = (c32 * KS + hw) * 8;
+  const int voff = v_lane<D>(gi, grp, hw);
+  const int klane = k_lane<D>(c32, hw);
 
   // The row's list (sparse), as in attn_fwd_kernel: its tiles, in list order,
   // a ragged block elsewhere than at the end left out, out-of-range entries
@@ -1210,7 +1200,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
     __syncthreads();
     f32x16 s_cur[2];
     if (n_mine > 0) {
-      qk_tile<D, KS, G>(sKV[0][sp], qf, c32, hw, s_cur);
+      qk_tile<D, G>(sKV[0][sp], klane, qf, s_cur);
       ref.template raise<G>(s_cur, sl2);
     }
     __syncthreads();            // slot 0 is refilled by step 0
@@ -1227,7 +1217,6 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
     bool bad = false;
     LD ld;
     ld.init(rg, lane);
-    const u32x4 rMw = ld.mixed_v ? rVw : rKw;
 
     // Step j of a wave is step t of attn_fwd_kernel on its own tiles.
     auto step = [&](int j) {
@@ -1254,17 +1243,16 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
       }
       uint32_t fill = lds_addr(sKV[j & 1][sp]);
       asm volatile("" : "+s"(fill));
-      const uint32_t mbyte = ld.mixed_v ? vbyte : kbyte;
       auto hook = [&](int slot) {       // loads in the first slots of the step
         static_assert(LD::PW <= 2 * G * NK, "one load instruction per slot at most");
-        if (slot < LD::PW) ld.issue_n(slot, fill, rKw, rVw, rMw, kbyte, vbyte, mbyte);
+        if (slot < LD::PW) ld.issue_n(slot, fill, rKw, rVw, kbyte, vbyte);
         if constexpr (BS)
           if (slot == G * NK) flush_waiting();
       };
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
       float tsum = 0.f;
-      pipelined_step<D, KS, VS, G, BS, true>(hook, rd + klane, rd + LD::VOFF + voff, qf, s_cur, p_prev, s_next,
+      pipelined_step<D, G, BS, true>(hook, rd, klane, rd + LD::VOFF, voff, qf, s_cur, p_prev, s_next,
                                              p_cur, o, sl2, ref.mc, rsum, &tsum);
       move_reference<G, BS>(ref, rsum, bad, p_cur, pend, pend_alpha, sl2, c32, &tsum);
       if constexpr (BS) {
@@ -1300,7 +1288,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) o[d][e] *= pend_alpha;
       }
-      pv_tile<ND, VS, G>(sKV[(n_mine - 1) & 1][sp] + LD::VOFF + voff, p_prev, o);
+      pv_tile<ND, G>(sKV[(n_mine - 1) & 1][sp] + LD::VOFF, voff, p_prev, o);
       lsum = finish_sums<G>(rsum, bad, p_prev, hw, c32);
       bad = bad || ref.m == -INFINITY || !acc_finite<ND>(o);
       redo = __any(bad);
@@ -1320,8 +1308,8 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
 
   // Remaining tiles, one at a time with key masking, loaded by all waves and
   // computed by those of one split (or by none that meet here).
-  using KAll = TileDMA<D, NS * RG, 1, KEYS>;
-  using VAll = TileDMA<D, NS * RG, 2, KEYS>;
+  using KAll = TileDMA<D, NS * RG, K_TILE, KEYS>;
+  using VAll = TileDMA<D, NS * RG, V_TILE, KEYS>;
   auto masked_tile = [&](int kb, bool compute) {
     KAll::issue(rK, sKV[0][0], kb, wave, lane);
     VAll::issue(rV, sKV[0][0] + LD::VOFF, kb, wave, lane);
@@ -1329,7 +1317,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
     __syncthreads();
     if (compute) {
       f32x16 s[2];
-      qk_tile<D, KS, G>(sKV[0][0], qf, c32, hw, s);
+      qk_tile<D, G>(sKV[0][0], klane, qf, s);
       mask_tile<G>(s, L - kb, hw);
       bf16x8 pb[2][2];
       float alpha;
@@ -1345,7 +1333,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
       for (int d = 0; d < ND; ++d)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[d][e] *= alpha;
-      pv_tile<ND, VS, G>(sKV[0][0] + LD::VOFF + voff, pb, o);
+      pv_tile<ND, G>(sKV[0][0] + LD::VOFF, voff, pb, o);
     }
     __syncthreads();
   };
@@ -1423,8 +1411,9 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
   mine *= total > 0.f ? 1.f / total : 0.f;
   // Partial outputs to LDS (the ring is free: every wave has passed the
   // barrier after its last read), then each thread adds whole 16-byte pieces.
-  constexpr int RS = D + 4;
-  static_assert(NS * kSplitRows * RS * 4 <= (int)sizeof(sKV), "the partial outputs fit the ring");
+  // A row's 16-byte chunks are in an order of its own, as in the tiles.
+  constexpr int C16 = D / 4;
+  static_assert(NS * kSplitRows * D * 4 <= (int)sizeof(sKV), "the partial outputs fit the ring");
   float* part = reinterpret_cast<float*>(&sKV[0][0][0]);
 #pragma unroll
   for (int d = 0; d < ND; ++d)
@@ -1433,7 +1422,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
       f32x4 v;
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = o[d][4 * i + j] * mine;
-      *reinterpret_cast<f32x4*>(part + (sp * kSplitRows + r) * RS + d * 32 + 8 * i + 4 * hw) = v;
+      *reinterpret_cast<f32x4*>(part + (sp * kSplitRows + r) * D + ((8 * d + 2 * i + hw) ^ (r & (C16 - 1))) * 4) = v;
     }
   __syncthreads();
 #pragma unroll
@@ -1442,11 +1431,12 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      const f32x4* p = reinterpret_cast<const f32x4*>(part + (s * kSplitRows + pr) * RS + ch * 8);
+      const f32x4* p = reinterpret_cast<const f32x4*>(part + (s * kSplitRows + pr) * D);
+      const f32x4 x = p[(2 * ch) ^ (pr & (C16 - 1))], y = p[(2 * ch + 1) ^ (pr & (C16 - 1))];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        lo[j] += p[0][j];
-        hi[j] += p[1][j];
+        lo[j] += x[j];
+        hi[j] += y[j];
       }
     }
     bf16x8 w;
@@ -1491,8 +1481,7 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
   constexpr int NT = 64 * NW;
   constexpr int WPB = NW / QB;       // waves per query block
   constexpr int SUB = 32 * WPB / KT; // KT-key tiles per key block
-  using KDMA = TileDMA<D, NW, 1>;
-  constexpr int KS = KDMA::S;
+  using KDMA = TileDMA<D, NW, K_TILE>;
   constexpr int NK = D / 16;
   constexpr int RING = kMassRing, CHUNK = 64;
 
@@ -1515,6 +1504,7 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
   const bool to_end = kb1 == a.nkb;
   const int t0 = kb0 * SUB;                             // the range's full key tiles [t0, nfull)
   const int nfull = to_end ? L / KT : kb1 * SUB;
+  const int klane = k_lane<D>(c32, hw);
   float* wrow = a.w + ((size_t)bh * a.nkb + p0) * a.nkb;    // row p0 + qb at wrow + qb * nkb
   const int nrows = a.nkb - p0 < QB ? a.nkb - p0 : QB;      // rows of W this group owns
 
@@ -1568,12 +1558,12 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
     wait_vmem();
     __syncthreads();
     f32x16 s_cur[2];
-    qk_tile<D, KS>(sK0, qf, c32, hw, s_cur);
+    qk_tile<D>(sK0, klane, qf, s_cur);
     __syncthreads();            // sK0 is refilled by the first step
 
     KLoader<D, NW> ld;
     ld.init(wave, lane);
-    const int klane = (c32 * KS + hw) * 8;
+    const int klane = k_lane<D>(c32, hw);
     // Step t (t + 1 < nfull) sums tile t, forms the scores of tile t+1 from
     // one buffer and loads tile t+2 into the other.
     // Past the last tile the load is clamped to the last one (an in-range
@@ -1597,7 +1587,7 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
         if (slot == NK && bdone >= 0) reduce_block(adone, bdone);
       };
       f32x16 s_next[2];
-      mass_step<D, KS>(hook, rdK + klane, qf, s_cur, s_next, acc, sl2, nlse2);
+      mass_step<D>(hook, rdK, klane, qf, s_cur, s_next, acc, sl2, nlse2);
       s_cur[0] = s_next[0];
       s_cur[1] = s_next[1];
       const int reduced = bdone;
@@ -1647,7 +1637,7 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
     wait_vmem();
     __syncthreads();
     f32x16 s[2];
-    qk_tile<D, KS>(sK0, qf, c32, hw, s);
+    qk_tile<D>(sK0, klane, qf, s);
     mask_tile(s, L - nfull * KT, hw);
 #pragma unroll
     for (int e = 0; e < 32; ++e) acc += fast_exp2(fmaf(s[e >> 4][e & 15], sl2, nlse2));
@@ -1664,8 +1654,8 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
 }
 
 template <int D, int QB, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void block_mass_kernel(MassParams a) {
-  using KDMA = TileDMA<D, NW, 1>;
+__global__ __launch_bounds__(64 * NW, 4) void block_mass_kernel(MassParams a) {
+  using KDMA = TileDMA<D, NW, K_TILE>;
   __shared__ __attribute__((aligned(1024))) u16 sK0[KDMA::ELEMS];
   __shared__ __attribute__((aligned(1024))) u16 sK1[KDMA::ELEMS];
   __shared__ float sRed[2][NW];           // per-wave sums of the last two blocks
@@ -1723,8 +1713,8 @@ template <int D, int QB>
 __global__ __launch_bounds__(512, 1) void fused_search_kernel(AttnParams a, MassParams m) {
   constexpr int NW = 8;
   using LD = KVLoader<D, NW>;
-  static_assert(TileDMA<D, NW, 1>::ELEMS <= LD::VOFF, "a mass K tile fits the K part of a ring slot");
-  static_assert((2 * NW + QB * kMassRing) * 4 <= TileDMA<D, NW, 2>::ELEMS * 2,
+  static_assert(TileDMA<D, NW, K_TILE>::ELEMS <= LD::VOFF, "a mass K tile fits the K part of a ring slot");
+  static_assert((2 * NW + QB * kMassRing) * 4 <= TileDMA<D, NW, V_TILE>::ELEMS * 2,
                 "the mass sums fit the V part of ring slot 0");
   attn_fwd_body<D, NW, false>(a, [&](int bh, int qt, const bf16x8 (&qf)[D / 16], float lt, float mref,
                                      u16* ring) {

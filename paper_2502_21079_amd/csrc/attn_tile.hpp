@@ -72,25 +72,33 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(size_t)(const __attribute__((address_space(3))) void*)p;
 }
 
-// One [KT, D] bf16 tile in LDS with padded rows: row r starts at chunk
-// r * S (16-byte chunks, S = D/8 + PADC).  The K tile has one pad chunk per
-// row, so 8 (or 16) consecutive rows read at the same column fall in distinct
-// banks; the V tile has two, so each group of 4 rows x 32 bytes read by a
-// transposed load covers distinct banks.  With constant strides every operand
-// address is one lane base plus a compile-time offset.
-// KEYS is 64 (KT), or 32 for the key-split attention kernel's d 128 tiles.
-template <int D, int NW, int PADC, int KEYS = KT>
+// One [KEYS, D] bf16 tile in LDS, its rows back to back and the 16-byte chunks
+// of a row in an order of the row's own: chunk c of row r sits at place
+// c ^ swz(r).  So 16 consecutive rows of a K tile read at one column fall in
+// distinct banks, and so do the four rows of 64 bytes that 32 lanes of a
+// transposed read of a V tile take; and a lane's operand addresses differ in
+// compile-time offsets and one exclusive or per column (k_lane, v_lane).  The
+// loads write LDS in lane order, so the order is made by what each lane loads.
+// (Rows padded by one and two chunks instead took 19 load instructions per
+// pair of tiles where these take 16 at d 64, and 35 for 32 at d 128.)
+enum { K_TILE = 1, V_TILE = 2 };
+template <int D, int NW, int KIND, int KEYS = KT>
 struct TileDMA {
-  static constexpr int CPR = D / 8;                 // data chunks per row
-  static constexpr int S = CPR + PADC;              // chunks per LDS row
-  static constexpr int NINST = (KEYS * S + 63) / 64;   // 64-slot DMA instructions
-  static constexpr int SLOTS = NINST * 64;          // chunk slots per tile, the last ones past its rows if
-                                                    // they do not fill whole instructions
-  static constexpr int ELEMS = SLOTS * 8;           // bf16 elements per tile
+  static constexpr int CPR = D / 8;                 // chunks per row
+  static constexpr int RPI = 64 / CPR;              // rows per 64-lane instruction
+  static constexpr int NINST = KEYS / RPI;
+  static constexpr int SLOTS = KEYS * CPR;          // chunks per tile
+  static constexpr int ELEMS = KEYS * D;            // bf16 elements per tile
+
+  __device__ __forceinline__ static int swz(int row) {
+    if (KIND == K_TILE) return D == 64 ? (row >> 1) & 7 : row & 15;
+    return D == 64 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
+  }
+  // Chunk of its row that slot p of the tile holds.
+  __device__ __forceinline__ static int chunk_of(int p) { return (p % CPR) ^ swz(p / CPR); }
 
   // Issue the loads of rows [kbase, kbase + KEYS).  Rows past the buffer's end
-  // and pad slots use an out-of-range offset: the load is skipped and the slot
-  // reads zero.
+  // are skipped by its bounds check: the slot keeps what it held.
   __device__ __forceinline__ static void issue(__amdgpu_buffer_rsrc_t r, u16* dst, int kbase,
                                                int wave, int lane) {
 #pragma unroll
@@ -98,188 +106,146 @@ struct TileDMA {
       const int i = i0 + wave;
       if (i < NINST) {
         const int p = i * 64 + lane;
-        const int row = p / S, ch = p % S;
-        const uint32_t off = ch < CPR ? (uint32_t)((kbase + row) * D + ch * 8) * 2u : 0xFFFFFFF0u;
+        const uint32_t off = (uint32_t)((kbase + p / CPR) * D + chunk_of(p) * 8) * 2u;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(dst + i * 64 * 8), 16, off, 0, 0, 0);
       }
     }
   }
 
   // Issue the loads of a dual tile: rows [0, 32) from keys [ka, ka + 32),
-  // rows [32, 64) from keys [kb, kb + 32) (both inside the sequence).  Pad
-  // slots use an out-of-range offset: the load is skipped.
+  // rows [32, 64) from keys [kb, kb + 32) (both inside the sequence).
   __device__ __forceinline__ static void issue_dual(__amdgpu_buffer_rsrc_t r, u16* dst, int ka, int kb,
                                                     int wave, int lane) {
 #pragma unroll
     for (int i0 = 0; i0 < NINST; i0 += NW) {
       const int i = i0 + wave;
       if (i < NINST) {
-        const int p = i * 64 + lane;
-        const int row = p / S, ch = p % S;
+        const int p = i * 64 + lane, row = p / CPR;
         const int key = row < 32 ? ka + row : kb + (row - 32);
-        const uint32_t off = ch < CPR ? (uint32_t)(key * D + ch * 8) * 2u : 0xFFFFFFF0u;
+        const uint32_t off = (uint32_t)(key * D + chunk_of(p) * 8) * 2u;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(dst + i * 64 * 8), 16, off, 0, 0, 0);
       }
     }
   }
 
-  // Byte offset, inside the tile, of the chunk that slot i * 64 + lane loads
-  // when every row of the tile lies inside the sequence.  A pad slot loads a
-  // copy of its row's last data chunk (it is never read, and an in-range
-  // duplicate keeps every offset below 2^16).
+  // Byte offset, inside a tile that lies whole in the sequence, of the chunk
+  // that slot i * 64 + lane holds.
   __device__ __forceinline__ static uint32_t rel_offset(int i, int lane) {
     const int p = i * 64 + lane;
-    const int row = p / S < KEYS ? p / S : KEYS - 1, ch = p % S;
-    return (uint32_t)(row * D + (ch < CPR ? ch : CPR - 1) * 8) * 2u;
-  }
-  // Instruction i of a full tile whose first byte is tile_byte: the offset
-  // inside the tile comes from rel_offset, the tile start is the scalar
-  // offset, so an issue costs no address arithmetic.
-  __device__ __forceinline__ static void issue_full(__amdgpu_buffer_rsrc_t r, u16* dst,
-                                                    uint32_t tile_byte, int i, uint32_t rel) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(dst + i * 64 * 8), 16, rel,
-                                             (int)tile_byte, 0, 0);
+    return (uint32_t)(p / CPR * D + chunk_of(p) * 8) * 2u;
   }
 };
 using std::integral_constant;
 
+// A lane's K operand address in a tile, in elements: row c32, chunk hw; its
+// chunk 2 ks + hw of row 32 g + c32 is at (k_lane ^ 16 ks) + 32 g D.
+template <int D>
+__device__ __forceinline__ int k_lane(int c32, int hw) {
+  return c32 * D + (hw ^ TileDMA<D, 1, K_TILE>::swz(c32)) * 8;
+}
+// A lane's transposed V read: row 4 hw + gi / 4, elements 16 (grp & 1) +
+// 4 (gi & 3); output block d of row r further down is at (v_lane ^ 32 d) + r D
+// (r a multiple of 8).
+template <int D>
+__device__ __forceinline__ int v_lane(int gi, int grp, int hw) {
+  const int row = 4 * hw + (gi >> 2);
+  const int chunk = (2 * (grp & 1) + ((gi & 3) >> 1)) ^ TileDMA<D, 1, V_TILE>::swz(row);
+  return row * D + chunk * 8 + 4 * (gi & 1);
+}
+
 // Loads of one full K tile per step (the block-mass pass), uniform over the
-// waves as in KVLoader below: wave w issues the tile's DMA instructions
-// j * NW + w, j = 0 .. PW-1, and repeats its entry of j - 1 where the list
-// runs out, so no load sits behind a branch.
+// waves: wave w issues the tile's DMA instructions j * NW + w, j = 0 .. PW-1.
+// Their in-tile offsets differ by whole periods of the row order, so one
+// register holds them all and the rest goes into the scalar offset.
 template <int D, int NW>
 struct KLoader {
-  using K = TileDMA<D, NW, 1>;
-  static constexpr int PW = (K::NINST + NW - 1) / NW;
-  static_assert(K::NINST >= NW, "a repeated entry must be a load of the same wave");
-  uint32_t rel[PW];          // per lane: in-tile source offset of load j
-  uint32_t wbase, wlast;     // LDS byte offsets of this wave's pieces of entries 0 and PW-1
+  using K = TileDMA<D, NW, K_TILE>;
+  static constexpr int PW = K::NINST / NW;
+  static constexpr int STEP = K::RPI * NW * D * 2;     // source bytes between a wave's loads
+  static_assert(K::NINST % NW == 0 && K::RPI * NW % 16 == 0, "every wave loads alike, whole periods apart");
+  uint32_t rel;              // per lane: in-tile source offset of load 0
+  uint32_t wbase;            // LDS byte offset of this wave's piece of load 0
 
   __device__ __forceinline__ void init(int wave, int lane) {
     wbase = (uint32_t)wave * 1024u;
-    wlast = wbase - (((PW - 1) * NW + wave >= K::NINST) ? (uint32_t)NW * 1024u : 0u);
-#pragma unroll
-    for (int j = 0; j < PW; ++j) {
-      int f = j * NW + wave;
-      if (f >= K::NINST) f -= NW;
-      rel[j] = K::rel_offset(f, lane);
-    }
+    rel = K::rel_offset(wave, lane);
   }
   // Load n (a constant once the caller's loop is unrolled) of the tile whose
   // first byte is kbyte into the tile at LDS byte address tile.
   template <int J = 0>
   __device__ __forceinline__ void issue_n(int n, uint32_t tile, u32x4 rK, uint32_t kbyte) const {
     if constexpr (J < PW) {
-      if (n == J) dma16<J * NW * 1024>(rK, tile + (J == PW - 1 ? wlast : wbase), rel[J], kbyte);
+      if (n == J) dma16<J * NW * 1024>(rK, tile + wbase, rel, kbyte + J * STEP);
       else issue_n<J + 1>(n, tile, rK, kbyte);
     }
   }
 };
 
-
 // Loads of one full K tile and one full V tile per step into one ring slot
-// laid out [K tile | V tile].  The 64-slot DMA instructions of the two tiles
-// form one list of NTOT = K::NINST + V::NINST entries, entry f writing the
-// f-th 1 KB piece of the slot, and wave w issues entry j * NW + w for j = 0
-// .. PW-1.  Every wave issues the same number of loads and none sits behind
-// a branch: where the list runs out (the last j of some waves) a wave repeats
-// its entry of j - 1 (the same data to the same place).  The source of a load
-// is the tile's first byte (scalar offset) plus a per-lane in-tile offset kept
-// in a register, and its destination the slot plus a per-wave constant.
-// Entries j with (j+1)*NW <= K::NINST are K loads for every wave, entries
-// with j*NW >= K::NINST are V loads for every wave, and the one j in between
-// (if any) is K for some waves and V for the others ("mixed").
+// laid out [K tile | V tile].  Wave w issues instructions j * NW + w of the K
+// tile (j < PWK), then those of the V tile, each filling a 1 KB piece of the
+// slot.  The source of a load is the tile's first byte and a constant (scalar
+// offset) plus a per-lane in-tile offset in a register, and its destination
+// the slot plus a per-wave constant.
 template <int D, int NW, int KEYS = KT>
 struct KVLoader {
-  using K = TileDMA<D, NW, 1, KEYS>;
-  using V = TileDMA<D, NW, 2, KEYS>;
-  static constexpr int NK = K::NINST;
-  static constexpr int NTOT = K::NINST + V::NINST;
-  static constexpr int PW = (NTOT + NW - 1) / NW;           // loads per wave and step
+  using K = TileDMA<D, NW, K_TILE, KEYS>;
+  using V = TileDMA<D, NW, V_TILE, KEYS>;
+  static constexpr int PWK = K::NINST / NW;                 // loads per wave, tile and step
+  static constexpr int PW = 2 * PWK;
   static constexpr int ELEMS = K::ELEMS + V::ELEMS;         // bf16 elements per ring slot
   static constexpr int VOFF = K::ELEMS;                     // V tile within the slot
-  static_assert(K::ELEMS == NK * 512, "the V tile starts right after the K tile's pieces");
-  static_assert(V::NINST >= NW, "a repeated entry must be a V load of the same wave");
-  static_assert(NK % NW == 0 || NK / NW != PW - 1, "the mixed entry is not the last one");
-  static_assert(KT * D * 2 <= 65536, "in-tile offsets must fit in 16 bits");
-  static constexpr bool all_k(int j) { return (j + 1) * NW <= NK; }
-  static constexpr bool all_v(int j) { return j * NW >= NK; }
+  static constexpr int ROWS = K::RPI * NW;                  // rows between a wave's loads
+  static constexpr int NP = ROWS % 16 == 0 ? 1 : 16 / ROWS; // loads until the K rows' order repeats
+  static_assert(K::NINST % NW == 0 && ROWS % 4 == 0 && 16 % (NP * ROWS < 16 ? NP * ROWS : 16) == 0,
+                "every wave loads alike, whole periods of the row orders apart");
+  static constexpr uint32_t row_bytes(int rows) { return (uint32_t)rows * D * 2u; }
 
-  uint32_t rel[PW];          // per lane: in-tile source offset of load j
+  uint32_t relK[NP], relV;   // per lane: in-tile source offsets, without their row of load j
   uint32_t wbase;            // LDS byte offset of this wave's piece of entry j = 0
-  uint32_t wlast;            // the same for the last entry (one row of pieces lower if it repeats)
-  bool mixed_v;              // the mixed entry is a V load for this wave
 
   __device__ __forceinline__ void init(int wave, int lane) {
     wbase = (uint32_t)wave * 1024u;
-    wlast = wbase - (((PW - 1) * NW + wave >= NTOT) ? (uint32_t)NW * 1024u : 0u);
-    mixed_v = (NK / NW) * NW + wave >= NK;
 #pragma unroll
-    for (int j = 0; j < PW; ++j) {
-      int f = j * NW + wave;
-      if (f >= NTOT) f -= NW;
-      rel[j] = f < NK ? K::rel_offset(f, lane) : V::rel_offset(f - NK, lane);
-    }
+    for (int j = 0; j < NP; ++j) relK[j] = K::rel_offset(j * NW + wave, lane) - row_bytes(j * ROWS);
+    relV = V::rel_offset(wave, lane);
   }
-  // Load J of this wave into the slot at LDS byte address slot; rK / rV are
-  // the K and V resources and rM the one of this wave's mixed entry, kbyte /
-  // vbyte / mbyte the first bytes of the K tile, the V tile and the mixed
-  // entry's tile.
+  // Load J of this wave into the slot at LDS byte address slot; kbyte / vbyte
+  // are the first bytes of the K and the V tile.
   template <int J>
-  __device__ __forceinline__ void issue(uint32_t slot, u32x4 rK, u32x4 rV, u32x4 rM, uint32_t kbyte,
-                                        uint32_t vbyte, uint32_t mbyte) const {
+  __device__ __forceinline__ void issue(uint32_t slot, u32x4 rK, u32x4 rV, uint32_t kbyte, uint32_t vbyte) const {
     constexpr int F = J * NW * 1024;
-    if constexpr (J == PW - 1) dma16<F>(rV, slot + wlast, rel[J], vbyte);
-    else if constexpr (all_k(J)) dma16<F>(rK, slot + wbase, rel[J], kbyte);
-    else if constexpr (all_v(J)) dma16<F>(rV, slot + wbase, rel[J], vbyte);
-    else dma16<F>(rM, slot + wbase, rel[J], mbyte);
+    if constexpr (J < PWK) dma16<F>(rK, slot + wbase, relK[J % NP], kbyte + row_bytes(J * ROWS));
+    else dma16<F>(rV, slot + wbase, relV, vbyte + row_bytes((J - PWK) * ROWS));
   }
   // Load n (a constant once the caller's loop is unrolled).
   template <int J = 0>
-  __device__ __forceinline__ void issue_n(int n, uint32_t slot, u32x4 rK, u32x4 rV, u32x4 rM, uint32_t kbyte,
-                                          uint32_t vbyte, uint32_t mbyte) const {
+  __device__ __forceinline__ void issue_n(int n, uint32_t slot, u32x4 rK, u32x4 rV, uint32_t kbyte,
+                                          uint32_t vbyte) const {
     if constexpr (J < PW) {
-      if (n == J) issue<J>(slot, rK, rV, rM, kbyte, vbyte, mbyte);
-      else issue_n<J + 1>(n, slot, rK, rV, rM, kbyte, vbyte, mbyte);
+      if (n == J) issue<J>(slot, rK, rV, kbyte, vbyte);
+      else issue_n<J + 1>(n, slot, rK, rV, kbyte, vbyte);
     }
   }
 
   // Dual slots: rows [0, 32) of the K and V tiles come from one 32-key half
-  // tile, rows [32, 64) from another.  Bit j of the returned mask is set when
-  // this lane's load j fills a row of the second half (the pieces and their
-  // assignment to the waves are those above).
-  __device__ __forceinline__ static uint32_t half_mask(int wave, int lane) {
-    uint32_t m = 0;
-#pragma unroll
-    for (int j = 0; j < PW; ++j) {
-      int f = j * NW + wave;
-      if (f >= NTOT) f -= NW;
-      const int row = f < NK ? (f * 64 + lane) / K::S : ((f - NK) * 64 + lane) / V::S;
-      if (row >= 32) m |= 1u << j;
-    }
-    return m;
-  }
-  // Load J of a dual slot: ka / va are the first bytes of the first half's
-  // K / V keys, kb / vb those of the second half's minus 32 rows (the in-tile
-  // offsets of its rows start at row 32), and the lane adds the one of the
-  // half its row belongs to; the scalar offset is zero.
+  // tile, rows [32, 64) from another; ka / va are the first bytes of the first
+  // half's K / V keys, kb / vb those of the second's.  All rows of a load
+  // belong to one half.
   template <int J>
-  __device__ __forceinline__ void issue_dual(uint32_t slot, u32x4 rK, u32x4 rV, u32x4 rM, uint32_t ka,
-                                             uint32_t kb, uint32_t va, uint32_t vb, uint32_t hmask) const {
-    constexpr int F = J * NW * 1024;
-    const bool second = (hmask >> J) & 1u;
-    const uint32_t kk = second ? kb : ka, vv = second ? vb : va;
-    if constexpr (J == PW - 1) dma16<F>(rV, slot + wlast, rel[J] + vv, 0u);
-    else if constexpr (all_k(J)) dma16<F>(rK, slot + wbase, rel[J] + kk, 0u);
-    else if constexpr (all_v(J)) dma16<F>(rV, slot + wbase, rel[J] + vv, 0u);
-    else dma16<F>(rM, slot + wbase, rel[J] + (mixed_v ? vv : kk), 0u);
+  __device__ __forceinline__ void issue_dual(uint32_t slot, u32x4 rK, u32x4 rV, uint32_t ka, uint32_t kb,
+                                             uint32_t va, uint32_t vb) const {
+    constexpr int F = J * NW * 1024, ROW = (J < PWK ? J : J - PWK) * ROWS;
+    static_assert(32 % ROWS == 0, "a load lies in one half");
+    if constexpr (J < PWK) dma16<F>(rK, slot + wbase, relK[J % NP], (ROW < 32 ? ka : kb) + row_bytes(ROW % 32));
+    else dma16<F>(rV, slot + wbase, relV, (ROW < 32 ? va : vb) + row_bytes(ROW % 32));
   }
   template <int J = 0>
-  __device__ __forceinline__ void issue_dual_n(int n, uint32_t slot, u32x4 rK, u32x4 rV, u32x4 rM, uint32_t ka,
-                                               uint32_t kb, uint32_t va, uint32_t vb, uint32_t hmask) const {
+  __device__ __forceinline__ void issue_dual_n(int n, uint32_t slot, u32x4 rK, u32x4 rV, uint32_t ka,
+                                               uint32_t kb, uint32_t va, uint32_t vb) const {
     if constexpr (J < PW) {
-      if (n == J) issue_dual<J>(slot, rK, rV, rM, ka, kb, va, vb, hmask);
-      else issue_dual_n<J + 1>(n, slot, rK, rV, rM, ka, kb, va, vb, hmask);
+      if (n == J) issue_dual<J>(slot, rK, rV, ka, kb, va, vb);
+      else issue_dual_n<J + 1>(n, slot, rK, rV, ka, kb, va, vb);
     }
   }
 };
@@ -317,17 +283,15 @@ __device__ __forceinline__ void load_q(const u16* qh, int qrow, int L, int hw, b
 
 // S^T tile for G groups of 32 keys (G = 2: a 64-key tile; G = 1: its first
 // 32 keys): lane (hw, c32) gets keys 32g + 8(e/4) + 4hw + e%4 of query c32 in
-// s[g][e].
-template <int D, int S, int G = 2>
-__device__ __forceinline__ void qk_tile(const u16* sK, const bf16x8 (&qf)[D / 16], int c32, int hw,
-                                        f32x16 (&s)[2]) {
-  const u16* base = sK + (c32 * S + hw) * 8;
+// s[g][e].  ka is the lane's k_lane.
+template <int D, int G = 2>
+__device__ __forceinline__ void qk_tile(const u16* sK, int ka, const bf16x8 (&qf)[D / 16], f32x16 (&s)[2]) {
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     s[g] = f32x16{};
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
-      bf16x8 kf = *reinterpret_cast<const bf16x8*>(base + (32 * g * S + 2 * ks) * 8);
+      bf16x8 kf = *reinterpret_cast<const bf16x8*>(sK + (ka ^ (16 * ks)) + 32 * g * D);
       s[g] = mfma32(kf, qf[ks], s[g]);
     }
   }
@@ -592,18 +556,18 @@ __device__ __forceinline__ float softmax_tile_fsum(const f32x16 (&s)[2], RowRef&
 // O^T += V^T P^T for one tile.  MFMA step (g, s2) covers keys
 // 32g + 16s2 + 8u + 4hw + j; lane (hw, e) supplies key index 8*(e/4) + 4*hw +
 // e%4 of the step.  In each 16-lane group, lane j names row r0 + j/4 and 4
-// elements at column d*32 + 16*(grp&1) + 4*(j%4); vlane is that lane's base.
-template <int ND, int VS, int G = 2>
-__device__ __forceinline__ void pv_tile(const u16* vlane, const bf16x8 (&pb)[2][2], f32x16 (&o)[ND]) {
+// elements at column d*32 + 16*(grp&1) + 4*(j%4); va is the lane's v_lane.
+template <int ND, int G = 2>
+__device__ __forceinline__ void pv_tile(const u16* sV, int va, const bf16x8 (&pb)[2][2], f32x16 (&o)[ND]) {
 #pragma unroll
   for (int d = 0; d < ND; ++d)
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) {
-        const u16* p0 = vlane + (32 * g + 16 * s2) * VS * 8 + d * 32;
+        const u16* p0 = sV + (va ^ (32 * d)) + (32 * g + 16 * s2) * (ND * 32);
         const s16x4 lo = lds_read_tr16(p0);
-        const s16x4 hi = lds_read_tr16(p0 + 8 * VS * 8);
+        const s16x4 hi = lds_read_tr16(p0 + 8 * (ND * 32));
         bf16x8 vf;
         __builtin_memcpy(&vf, &lo, 8);
         __builtin_memcpy(reinterpret_cast<char*>(&vf) + 8, &hi, 8);
@@ -613,14 +577,15 @@ __device__ __forceinline__ void pv_tile(const u16* vlane, const bf16x8 (&pb)[2][
 
 // Writes one wave's 32 x D output tile (o scaled by inv, rounded to bf16) as
 // whole rows: the tile goes through stage, this wave's region of the K/V ring
-// (32 rows of D + 8 elements, free once every wave has passed a barrier
-// after its last use of the ring), and each store instruction then writes
-// 64 / (D / 8) complete rows of 2 D bytes instead of 8-byte pieces of 32
-// rows.  Row row0 + r of out gets tile row r; rows at or past L are skipped.
+// (32 rows of D elements, their 16-byte chunks in an order of the row's own as
+// in the tiles; free once every wave has passed a barrier after its last use
+// of the ring), and each store instruction then writes 64 / (D / 8) complete
+// rows of 2 D bytes instead of 8-byte pieces of 32 rows.  Row row0 + r of out
+// gets tile row r; rows at or past L are skipped.
 template <int D>
 __device__ __forceinline__ void store_rows(const f32x16 (&o)[D / 32], float inv, u16* stage, u16* out,
                                            int row0, int L, int lane) {
-  constexpr int ND = D / 32, RS = D + 8, CPR = D / 8, RPI = 64 / CPR;
+  constexpr int ND = D / 32, CPR = D / 8, RPI = 64 / CPR;
   const int hw = lane >> 5, c32 = lane & 31;
 #pragma unroll
   for (int d = 0; d < ND; ++d)
@@ -629,17 +594,17 @@ __device__ __forceinline__ void store_rows(const f32x16 (&o)[D / 32], float inv,
       bf16x4 w;
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[j] = (__bf16)(o[d][4 * i + j] * inv);
-      *reinterpret_cast<bf16x4*>(stage + c32 * RS + d * 32 + 8 * i + 4 * hw) = w;
+      *reinterpret_cast<bf16x4*>(stage + c32 * D + ((4 * d + i) ^ (c32 & (CPR - 1))) * 8 + 4 * hw) = w;
     }
 #pragma unroll 4
   for (int j = 0; j < 32 / RPI; ++j) {
     const int r = lane / CPR + RPI * j;
-    const bf16x8 v = *reinterpret_cast<const bf16x8*>(stage + r * RS + (lane % CPR) * 8);
+    const bf16x8 v = *reinterpret_cast<const bf16x8*>(stage + r * D + ((lane ^ r) & (CPR - 1)) * 8);
     if (row0 + r < L) *reinterpret_cast<bf16x8*>(out + (size_t)(row0 + r) * D + (lane % CPR) * 8) = v;
   }
 }
 template <int D, int NW>
-constexpr int kStageElems = NW * 32 * (D + 8);    // ring elements store_rows uses
+constexpr int kStageElems = NW * 32 * D;    // ring elements store_rows uses
 
 // One pipelined step, scheduled by hand: NM = 2*NK + 4*ND MFMA slots that
 // alternate a QK MFMA (scores of the next tile) and a PV MFMA (output update
@@ -661,8 +626,8 @@ constexpr int kStageElems = NW * 32 * (D + 8);    // ring elements store_rows us
 // middle).  The sums are the same either way.
 // With BS, *tsum receives this lane's sum of the current tile's unrounded
 // exponentials, added pair by pair as the pairs are rounded.
-template <int D, int KS, int VS, int G = 2, bool BS = false, bool RS_FIRST = false, typename Hook>
-__device__ __forceinline__ void pipelined_step(Hook&& hook, const u16* klane, const u16* vlane,
+template <int D, int G = 2, bool BS = false, bool RS_FIRST = false, typename Hook>
+__device__ __forceinline__ void pipelined_step(Hook&& hook, const u16* sK, int ka, const u16* sV, int va,
                                                const bf16x8 (&qf)[D / 16], const f32x16 (&s_cur)[2],
                                                const bf16x8 (&p_prev)[2][2], f32x16 (&s_next)[2],
                                                bf16x8 (&p_cur)[2][2], f32x16 (&o)[D / 32], float sl2,
@@ -680,12 +645,12 @@ __device__ __forceinline__ void pipelined_step(Hook&& hook, const u16* klane, co
     const int j = i >> 1;
     if ((i & 1) == 0) {       // QK j: g = j / NK, ks = j % NK
       const int g = j / NK, ks = j % NK;
-      op[i] = *reinterpret_cast<const bf16x8*>(klane + (32 * g * KS + 2 * ks) * 8);
+      op[i] = *reinterpret_cast<const bf16x8*>(sK + (ka ^ (16 * ks)) + 32 * g * D);
     } else {                  // PV j: d = j % ND, (g, s2) = j / ND
       const int d = j % ND, g = (j / ND) >> 1, s2 = (j / ND) & 1;
-      const u16* p0 = vlane + (32 * g + 16 * s2) * VS * 8 + d * 32;
+      const u16* p0 = sV + (va ^ (32 * d)) + (32 * g + 16 * s2) * D;
       const s16x4 lo = lds_read_tr16(p0);
-      const s16x4 hi = lds_read_tr16(p0 + 8 * VS * 8);
+      const s16x4 hi = lds_read_tr16(p0 + 8 * D);
       __builtin_memcpy(&op[i], &lo, 8);
       __builtin_memcpy(reinterpret_cast<char*>(&op[i]) + 8, &hi, 8);
     }
@@ -769,15 +734,21 @@ __device__ __forceinline__ void pipelined_step(Hook&& hook, const u16* klane, co
 // next tile (alternating the two 32-key groups) with, slot by slot, an equal
 // share of the exp2(s * sl2 - lse2) terms of the current tile added to acc in
 // (group, element) order; hook(slot) issues the caller's tile loads.
-template <int D, int KS, typename Hook>
-__device__ __forceinline__ void mass_step(Hook&& hook, const u16* klane, const bf16x8 (&qf)[D / 16],
+template <int D, typename Hook>
+__device__ __forceinline__ void mass_step(Hook&& hook, const u16* sK, int ka, const bf16x8 (&qf)[D / 16],
                                           const f32x16 (&s_cur)[2], f32x16 (&s_next)[2], float& acc,
                                           float sl2, float nlse2) {
   constexpr int NK = D / 16, NM = 2 * NK, LA = 2;
   bf16x8 op[NM];
+  // At d 128 half of the columns' addresses are formed in every step: kept over
+  // the loop, all eight would take the pass past 128 registers.
+  int half_row = 64;
+  if constexpr (D == 128) asm volatile("" : "+s"(half_row));
   auto fetch = [&](int j) {
     const int g = j & 1, ks = j >> 1;
-    op[j] = *reinterpret_cast<const bf16x8*>(klane + (32 * g * KS + 2 * ks) * 8);
+    int at = ka ^ (16 * (ks & 3));
+    if (ks >= 4) at ^= half_row;
+    op[j] = *reinterpret_cast<const bf16x8*>(sK + at + 32 * g * D);
   };
   auto mfma = [&](int j) {
     const int g = j & 1, ks = j >> 1;
