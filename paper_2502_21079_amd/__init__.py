@@ -22,6 +22,7 @@ import ctypes
 import functools
 import os
 from dataclasses import dataclass
+from operator import index
 from typing import Optional, Sequence
 
 import torch
@@ -143,14 +144,15 @@ def _stream(device):
 
 
 # The argument structures of a call are made once per set of values (sizes and
-# parameters, never tensors) and only read from then on, by the library too.
+# parameters as plain numbers, never tensors or other objects that hash by
+# identity) and only read from then on, by the library too.
 @functools.lru_cache(maxsize=256, typed=True)
 def _problem_ref(B, H, L, D, block, text_start, text_len, scale):
     return ctypes.byref(_Problem(B, H, L, D, block, text_start, text_len, scale))
 
 
 def _problem(shape, block: int, text_start: int, text_len: int, scale: Optional[float]):
-    return _problem_ref(*shape, block, text_start, text_len, 0.0 if scale is None else float(scale))
+    return _problem_ref(*map(index, (*shape, block, text_start, text_len)), 0.0 if scale is None else float(scale))
 
 
 def _check_qkv(*ts):
@@ -195,10 +197,11 @@ def _search_args(shape, block, text_start, text_len, scale, mode, head_param_bp,
     params = tuple([int(x) for x in head_param_bp]) if head_param_bp is not None else ()
     # The library reads head_param_bp[0 .. H-1] in the per-head modes: a shorter
     # list would be read past its end.
+    shape = tuple(shape)
     if mode != "hierarchical" and len(params) != shape[1]:
         raise AdaspaError(f"head_param_bp needs one entry per head ({shape[1]}), got {len(params)}")
     flags = (F_TEXT_SINK if text_sink else 0) | (F_SCORES_GIVEN if scores_given else 0)
-    return _search_plan(*shape, block, text_start, text_len, 0.0 if scale is None else float(scale),
+    return _search_plan(*map(index, (*shape, block, text_start, text_len)), 0.0 if scale is None else float(scale),
                         _MODES[mode], flags, params, int(base_sparsity_bp), int(recall_threshold_bp))
 
 

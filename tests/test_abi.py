@@ -342,3 +342,18 @@ def test_workspace_tensors_count_in_bytes():
         ad._workspace_bytes(torch.empty(8, 2, dtype=torch.uint8).t(), cpu)
     with pytest.raises(ad.AdaspaError):
         ad._workspace_bytes(torch.empty(8, dtype=torch.uint8), torch.device("cuda", 0))
+
+
+def test_cached_sizes_follow_values_not_objects():
+    """The binding keeps sizes per set of values: an integer tensor or array
+    element passed as a size counts with the value it holds at the call."""
+    n = torch.tensor(64)
+    args = ((1, 2, 2048, 64), 64, 0)
+    first = ad.block_search_capacity(*args, n, "topk", [2000, 2000])
+    n.fill_(1024)
+    second = ad.block_search_capacity(*args, n, "topk", [2000, 2000])
+    assert first == ad.block_search_capacity(*args, 64, "topk", [2000, 2000])
+    assert second == ad.block_search_capacity(*args, 1024, "topk", [2000, 2000]) != first
+    assert ad.block_search_capacity(iter((1, 2, 2048, 64)), 64, 0, 64, "topk", [2000, 2000]) == first
+    with pytest.raises(TypeError):
+        ad.block_search_capacity((1, 2, 2048, 64), 64.0, 0, 64, "topk", [2000, 2000])
