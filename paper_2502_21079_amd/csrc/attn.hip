@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
 // groups of 32, and four waves share the keys of each group: 128-key units
 // go round the four splits, so a step covers four tiles and the walk is a
 // quarter as long.  A tile is 64 keys at d 64 and 32 at d 128: two ring slots
-// of four [K | V] tiles take 152 KB and 144 KB of the CU's 160 KB.  Each
+// of four [K | V] tiles take 128 KB of the CU's 160 KB.  Each
 // wave is the pipeline of attn_fwd_kernel over its own tiles, with its own
 // softmax reference; at the end the four partial outputs of a row are scaled
 // to the largest reference and the row's whole sum (each to its share of the

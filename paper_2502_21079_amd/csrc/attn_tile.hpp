@@ -458,7 +458,7 @@ __device__ __forceinline__ void first_reference(RowRef& ref, const f32x16 (&s_cu
 // its probabilities are taken, and the registers of its two 32-key groups go
 // to the next tile's scores group by group; taking the probabilities again
 // against the new reference kept all of them to the end of every step (dense
-// attention at d 64: 182 registers, now 160).  bad is set when a sum has left
+// attention at d 64: 182 registers, now 163).  bad is set when a sum has left
 // the safe range.  A row's first reference is set before the pipeline from its
 // first tile; a row that has none then (no finite score) is redone on the
 // exact path (block-64 pairs, whose first tile may be the other block's, look
