@@ -74,20 +74,26 @@ struct NoTail {
 // for every 64 keys of its row's list and `fixed` more (fitted to 8,192 to
 // 32,768 tokens, 768 to 2,048 tiles, 4 to 30% kept; at 10%, one way against
 // the other: 16,384 tokens x 4 heads 168 -> 86 us at d 64 and 226 -> 154 us at
-// d 128, 8,192 tokens x 12 heads 89 -> 80 and 121 -> 117).  Only the device
+// d 128, 8,192 tokens x 12 heads 89 -> 80 and 121 -> 117).  The split kernel has
+// to look better by `margin` percent: it takes about 15% more than its model,
+// and the walk at d 128 about 8% more than its own, 15% in pairs of blocks of 64,
+// whose text rows share the CU with other pairs for longer (10%, d 128: 20,000
+// tokens x 8 heads 341 -> 296 us in blocks of 64 and 314 -> 292 of 128, 30,011 x
+// 6 520 -> 454 and 474 -> 440, against 15% everywhere).  Only the device
 // knows the lists' lengths, so both kernels are launched and the one that is
 // not to run returns at once (1-3 us).
 constexpr int kPickMaxTiles = 4096;
 struct PickCost {
   int walk, tile, fixed;      // in units of 1/100 us
+  int margin;                 // percent
 };
-__host__ __device__ constexpr PickCost pick_cost(int head_dim) {
-  return head_dim == 64 ? PickCost{72, 29, 700} : PickCost{92, 55, 800};
+__host__ __device__ constexpr PickCost pick_cost(int head_dim, int block) {
+  return head_dim == 64 ? PickCost{72, 29, 700, 15} : PickCost{92, 55, 800, block == 64 ? 0 : 8};
 }
-// Whether the split kernel is expected to be faster by 15% and more, the rows'
-// lists adding up to nnz64 times 64 keys over `rows` lists.
+// Whether the split kernel is expected to be faster by the margin and more, the
+// rows' lists adding up to nnz64 times 64 keys over `rows` lists.
 __host__ __device__ inline bool split_pays(PickCost c, int64_t tiles, int64_t nf, int64_t nnz64, int64_t rows) {
-  return tiles * (c.tile * nnz64 + c.fixed * rows) / 20 * 23 < 256 * rows * (c.walk * nf + 800);
+  return tiles * (c.tile * nnz64 + c.fixed * rows) / 100 * (100 + c.margin) < 256 * rows * (c.walk * nf + 800);
 }
 template <int D>
 __device__ __forceinline__ bool pick_key_split(const AttnParams& a) {
@@ -95,7 +101,7 @@ __device__ __forceinline__ bool pick_key_split(const AttnParams& a) {
   const int64_t end = a.row_ptr[rows];
   const int64_t nnz = end < 0 ? 0 : (end > a.col_count ? a.col_count : end);
   const int64_t text = (int64_t)a.row_ptr[a.text_block + 1] - a.row_ptr[a.text_block];
-  return text * rows >= 3 * nnz && split_pays(pick_cost(D), (int64_t)a.batch_heads * ((a.seqlen + 63) / 64),
+  return text * rows >= 3 * nnz && split_pays(pick_cost(D, a.block), (int64_t)a.batch_heads * ((a.seqlen + 63) / 64),
                                               a.seqlen / 64, nnz * (a.block / 64), rows);
 }
 
@@ -1901,7 +1907,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   const int64_t nf = a.seqlen / 64, rows = (int64_t)a.batch_heads * a.nkb, all = rows * a.nkb;
   const int64_t nnz = a.col_count < all ? a.col_count : all / 100 * 12;
   if (a.tq1 > a.tq0 && tiles <= kPickMaxTiles &&
-      split_pays(pick_cost(D), tiles, nf, nnz * (a.block / 64), rows)) {    // see pick_key_split
+      split_pays(pick_cost(D, a.block), tiles, nf, nnz * (a.block / 64), rows)) {    // see pick_key_split
     a.pick = PICK_SPLIT;
     const hipError_t e = launch_split<true, false>(a, D, st);
     if (e != hipSuccess) return e;
