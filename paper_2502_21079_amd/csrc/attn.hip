@@ -65,8 +65,11 @@ struct NoTail {
   __device__ __forceinline__ void operator()(T&&...) const {}
 };
 
+constexpr int kSplits = 4;            // waves that share a row's keys
+constexpr int kSplitRows = 64;        // query rows per workgroup of the key-split kernel
+
 // Block-sparse problems between the two ways (more tiles of 64 query rows than
-// use_key_split takes, with a text range).  When the text query rows keep
+// use_key_split takes).  When the text query rows keep
 // several times the blocks of the average row, they are the critical path of
 // the kernels that walk a row in one workgroup: about `walk` us for each 64
 // keys of the sequence and 8 more.  The key-split kernel walks them four times
@@ -79,30 +82,43 @@ struct NoTail {
 // and the walk at d 128 about 8% more than its own, 15% in pairs of blocks of 64,
 // whose text rows share the CU with other pairs for longer (10%, d 128: 20,000
 // tokens x 8 heads 341 -> 296 us in blocks of 64 and 314 -> 292 of 128, 30,011 x
-// 6 520 -> 454 and 474 -> 440, against 15% everywhere).  Only the device
-// knows the lists' lengths, so both kernels are launched and the one that is
-// not to run returns at once (1-3 us).
+// 6 520 -> 454 and 474 -> 440, against 15% everywhere).
+//
+// The two ways round differently, so the choice follows the shape and the
+// pattern alone: neither the text range that a call names nor the room in its
+// col_idx decides, and one pattern has one result.  Only the device knows the
+// lists' lengths, so within the shapes where a pattern of few blocks could take
+// the split kernel both kernels are launched, and the one that is not to run
+// returns at once (2-4 us at 640 to 4,096 tiles).  The text rows are looked for
+// at the two ends of the sequence, where models put their text: the longer of
+// the first and the last row of the first head.
 constexpr int kPickMaxTiles = 4096;
+constexpr int kPickFewest = 4;  // percent of the blocks, the fewest a pattern is expected to keep
 struct PickCost {
   int walk, tile, fixed;      // in units of 1/100 us
   int margin;                 // percent
 };
-__host__ __device__ constexpr PickCost pick_cost(int head_dim, int block) {
+static PickCost pick_cost(int head_dim, int block) {
   return head_dim == 64 ? PickCost{72, 29, 700, 15} : PickCost{92, 55, 800, block == 64 ? 0 : 8};
 }
-// Whether the split kernel is expected to be faster by the margin and more, the
-// rows' lists adding up to nnz64 times 64 keys over `rows` lists.
-__host__ __device__ inline bool split_pays(PickCost c, int64_t tiles, int64_t nf, int64_t nnz64, int64_t rows) {
-  return tiles * (c.tile * nnz64 + c.fixed * rows) / 100 * (100 + c.margin) < 256 * rows * (c.walk * nf + 800);
+// The most entries with which the split kernel is expected to be faster by the
+// margin and more; 0 for a shape whose patterns never take it.
+static int64_t pick_entries(const AttnParams& a, int head_dim) {
+  const PickCost c = pick_cost(head_dim, a.block);
+  const int64_t tiles = (int64_t)a.batch_heads * ((a.seqlen + kSplitRows - 1) / kSplitRows), nf = a.seqlen / 64;
+  if (tiles > kPickMaxTiles) return 0;
+  const int64_t rows = (int64_t)a.batch_heads * a.nkb;
+  const int64_t per_tile = 256 * (c.walk * nf + 800) * 100 / (tiles * (100 + c.margin)) - c.fixed;
+  const int64_t most = per_tile <= 0 ? 0 : per_tile * rows / (c.tile * (a.block / 64));
+  return most >= rows * a.nkb / 100 * kPickFewest ? most : 0;
 }
-template <int D>
+// The same choice in every workgroup of both kernels.
 __device__ __forceinline__ bool pick_key_split(const AttnParams& a) {
   const int64_t rows = (int64_t)a.batch_heads * a.nkb;
   const int64_t end = a.row_ptr[rows];
-  const int64_t nnz = end < 0 ? 0 : (end > a.col_count ? a.col_count : end);
-  const int64_t text = (int64_t)a.row_ptr[a.text_block + 1] - a.row_ptr[a.text_block];
-  return text * rows >= 3 * nnz && split_pays(pick_cost(D, a.block), (int64_t)a.batch_heads * ((a.seqlen + 63) / 64),
-                                              a.seqlen / 64, nnz * (a.block / 64), rows);
+  const int64_t first = (int64_t)a.row_ptr[1] - a.row_ptr[0];
+  const int64_t last = (int64_t)a.row_ptr[a.nkb] - a.row_ptr[a.nkb - 1];
+  return end >= 0 && end <= a.pick_entries && (first > last ? first : last) * rows >= 3 * end;
 }
 
 // With BS (dense only) the body also writes, for every row and key block c,
@@ -134,7 +150,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   // is given.
   int bh, qt;
   if constexpr (SPARSE) {
-    if (a.pick == PICK_OTHERS && pick_key_split<D>(a)) return;
+    if (a.pick == PICK_OTHERS && pick_key_split(a)) return;
     int item = (int)blockIdx.x;
     if (item >= a.n_static) {                // the queued tail (see claim_item)
       __shared__ int s_tail;
@@ -605,7 +621,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
 
   int bh, pq;
   {
-    if (a.pick == PICK_OTHERS && pick_key_split<D>(a)) return;
+    if (a.pick == PICK_OTHERS && pick_key_split(a)) return;
     int item = (int)blockIdx.x;
     if (item >= a.n_static) {                // as in attn_fwd_kernel
       __shared__ int s_tail;
@@ -1043,9 +1059,6 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
 // block-sparse (20%, block 64) 29 -> 15 us; a step takes about 1.1 us, of which
 // the four tiles' loads are half and their latency most of the rest.
 // ---------------------------------------------------------------------------
-constexpr int kSplits = 4;            // waves that share a row's keys
-constexpr int kSplitRows = 64;        // query rows per workgroup
-
 template <int D, bool SPARSE, bool BS>
 __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
   static_assert(!(SPARSE && BS), "block masses come from the dense pass");
@@ -1062,7 +1075,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
 
   int bh, qt;                                              // head, 64-row tile
   if constexpr (SPARSE) {
-    if (a.pick == PICK_SPLIT && !pick_key_split<D>(a)) return;
+    if (a.pick == PICK_SPLIT && !pick_key_split(a)) return;
     text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
   } else {
     int lid = xcd_remap((int)blockIdx.x, a.n_items);
@@ -1903,11 +1916,8 @@ static hipError_t plan_sparse_items(AttnParams& a, int D, hipStream_t st) {
 
 hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   if (a.split) return launch_split<true, false>(a, D, st);
-  const int64_t tiles = (int64_t)a.batch_heads * ((a.seqlen + kSplitRows - 1) / kSplitRows);
-  const int64_t nf = a.seqlen / 64, rows = (int64_t)a.batch_heads * a.nkb, all = rows * a.nkb;
-  const int64_t nnz = a.col_count < all ? a.col_count : all / 100 * 12;
-  if (a.tq1 > a.tq0 && tiles <= kPickMaxTiles &&
-      split_pays(pick_cost(D, a.block), tiles, nf, nnz * (a.block / 64), rows)) {    // see pick_key_split
+  a.pick_entries = pick_entries(a, D);
+  if (a.pick_entries > 0) {
     a.pick = PICK_SPLIT;
     const hipError_t e = launch_split<true, false>(a, D, st);
     if (e != hipSuccess) return e;

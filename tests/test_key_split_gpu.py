@@ -190,3 +190,32 @@ def test_sparse_pick_by_density(D, block, kept, room):
         idx = torch.as_tensor(rows, device="cuda")
         check_out(out[0, h, idx], o_ref, f"h{h}")
         check_lse(lse[0, h, idx], l_ref, f"h{h}")
+
+
+# (tokens, heads, blocks of 128 kept per video row): patterns that take the
+# key split, that are too dense for it, and between the two.
+@pytest.mark.parametrize("D,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("L,heads,kept", [(9000, 5, 3), (9000, 5, 30), (16384, 12, 6), (12001, 6, 12)])
+@pytest.mark.parametrize("text_first", [True, False])
+def test_sparse_results_follow_the_pattern_alone(D, block, L, heads, kept, text_first):
+    """A pattern has one result: bit for bit the same whatever text range the
+    call names (the right one, none, or one at the other end) and whatever
+    room its col_idx has past the last entry."""
+    w = _w(D, L, heads=heads, block=block, text=200)
+    q, k, v = make_qkv(w, device="cuda")
+    nb = w.nblocks
+    t0 = 0 if text_first else L - 200
+    tb = text_blocks(L, block, t0, 200)
+    g = np.random.default_rng(kept + D)
+    n = kept * (128 // block)
+    lists = [list(range(nb)) if r % nb in tb else
+             sorted(set(tb) | set(g.choice(nb, n, replace=False).tolist())) for r in range(heads * nb)]
+    rp, ci = _csr(lists)
+    roomy = torch.cat([ci, ci.new_full((heads * nb * nb - ci.numel(),), -7)])
+    base = None
+    for cols in (ci, roomy):
+        for start, n_text in ((t0, 200), (0, 0), (L - 200 - t0, 200)):
+            res = ad.block_sparse_attn(q, k, v, rp, cols, block=block, text_start=start, text_len=n_text)
+            base = base or res
+            torch.cuda.synchronize()
+            assert torch.equal(res[0], base[0]) and torch.equal(res[1], base[1]), (cols.numel(), start, n_text)
