@@ -34,6 +34,7 @@ struct AttnParams {
   bool split;                 // the key-split kernel takes the problem (use_key_split)
   int n_tail;                 // dense: the last items of this launch that run key-split (split_tail)
   int pick;                   // sparse: which patterns a launch runs (PICK_*, set by the launcher)
+  bool ends_first;            // sparse, key-split: the tiles at both ends first (set by the launcher)
   int64_t pick_entries;       // sparse: with PICK_*, the most entries of a pattern that runs key-split
   uint32_t* claim;            // 9 work-queue counters (one per XCD + a flag), or null
   int n_items;                // work items: (head, query tile) or (head, query block / pair)
