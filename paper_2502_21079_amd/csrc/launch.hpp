@@ -60,23 +60,28 @@ inline bool use_key_split(int64_t batch_heads, int seqlen) {
   return batch_heads * ((seqlen + 63) / 64) <= kSplitMaxTiles;
 }
 
-// Beyond that, dense attention runs one (head, 256-row tile) item per CU at a
-// time.  When the items leave a last round of few items, those run key-split
-// instead, four workgroups each: the number of such items, always the last
-// ones.  Up to 64 items fill one round of the split kernel, about a third of a
-// whole round, and at d 64 two thirds for up to 128, where a nearly empty
-// round of whole items takes 0.65 (d 128) and 0.77 (d 64) of a full one.  After
-// many rounds the CUs no longer end together and the last items hide among the
-// others' ends, so this stops at four whole rounds.  Dense, us, before and
-// after: 8,192 tokens x 9 heads (one round and 32 items) 240 -> 178 at d 64 and
-// 357 -> 291 at d 128; 35,000 x 4 (two and 36) 1492 -> 1282 and 2362 -> 2121;
-// 11,000 x 24 (four and 8) 819 -> 778 and 1284 -> 1276; but
-// 110,336 x 3 (five and 13) gained nothing and 17,920 x 48 (thirteen and 32,
-// d 64) 3825 -> 3932.
+// Beyond that, dense attention runs (head, 256-row tile) items, 256 at a time
+// at d 128 (one workgroup per CU); at d 64 an item is two workgroups of 128
+// rows, three of which share a CU, so up to 384 run at a time.  When the items
+// come to a few more than a multiple of 256, those few run key-split instead,
+// four workgroups each: the number of such items, always the last ones.
+// Dense, us, without and with it:
+// - d 128, where they are a last round of their own: 8,192 tokens x 9 heads (one
+//   round and 32 items) 358 -> 284, x 10 (and 64) 359 -> 297, 16,384 x 5 (and
+//   64) 706 -> 577, 35,000 x 4 (two and 36) 2410 -> 2095, 8,192 x 33 (four and
+//   32) 985 -> 941; after many rounds the CUs no longer end together and the
+//   last items hide among the others' ends, 110,336 x 3 (five and 13) gained
+//   nothing, so this stops at four;
+// - d 64, where they make CUs hold one workgroup more than others for their
+//   whole time: 8,192 x 9 177 -> 173, 35,000 x 4 1275 -> 1239, 16,384 x 13 (three
+//   and 64) 852 -> 836.  Below 8,192 tokens the second launch costs more
+//   (4,096 x 17 90.4 -> 91.6), and 65 to 128 items are slower at every length
+//   (8,192 x 12 198 -> 220, 35,000 x 8 2351 -> 2475).
 inline int split_tail(int64_t batch_heads, int seqlen, int head_dim) {
   const int64_t n = batch_heads * ((seqlen + 255) / 256), rest = n % 256;
   if (use_key_split(batch_heads, seqlen) || n < 256 || n / 256 > 4) return 0;
-  return rest <= (head_dim == 64 ? 128 : 64) ? (int)rest : 0;
+  if (head_dim == 64 && seqlen < 8192) return 0;
+  return rest <= 64 ? (int)rest : 0;
 }
 
 struct MassParams {

@@ -121,10 +121,10 @@ def test_one_split_on_the_exact_path(D):
         check_lse(lse[0, h], l_ref, f"h{h}")
 
 
-# Items of 256 rows: 256 + 64 (the most that run key-split at d 128), + 65
-# (none there, all at d 64), + 128 and + 129 (the same at d 64), + 1.
+# Items of 256 rows: 256 + 64 (the most that run key-split) and + 65 (none) at
+# either d, at d 64 just below the length from which they do, + 128, + 129, + 1.
 @pytest.mark.parametrize("D,heads,L", [(128, 20, 4090), (128, 107, 700), (64, 107, 700), (64, 24, 4000), (64, 77, 1200),
-                                       (128, 257, 70)])
+                                       (128, 257, 70), (64, 10, 8192), (64, 10, 8191), (64, 3, 27301)])
 def test_tail_items(D, heads, L):
     """The last items of a launch that fills the chip once: every entry point
     splits the same rows (outputs equal bit for bit), whatever the groups the
