@@ -502,6 +502,7 @@ adaspa_status adaspa_block_sparse_attn(const adaspa_problem* prob, const void* q
   a.scale = scale_of(prob);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   a.split = key_split(prob);
+  a.n_tail = key_split_tail(prob);
   a.claim = (uint32_t*)workspace;
   // Text query blocks keep every key block under the text sink, so they are
   // the longest rows; the kernel starts them first (the result does not

@@ -118,13 +118,23 @@ static int64_t pick_entries(const AttnParams& a, int head_dim) {
   const int64_t most = per_tile <= 0 ? 0 : per_tile * rows / (c.tile * (a.block / 64));
   return most >= rows * a.nkb / 100 * kPickFewest ? most : 0;
 }
-// The same choice in every workgroup of both kernels.
-__device__ __forceinline__ bool pick_key_split(const AttnParams& a) {
+// Which rows of a pattern run key-split: the same answer in every workgroup of
+// both kernels.  A pattern that keeps every block splits the rows that dense
+// attention splits (n_tail), so that the two agree bit for bit.
+enum { SPLIT_NONE = 0, SPLIT_TAIL = 1, SPLIT_ALL = 2 };
+__device__ __forceinline__ int split_rows(const AttnParams& a) {
   const int64_t rows = (int64_t)a.batch_heads * a.nkb;
   const int64_t end = a.row_ptr[rows];
+  if (a.n_tail > 0 && end == rows * a.nkb) return SPLIT_TAIL;
   const int64_t first = (int64_t)a.row_ptr[1] - a.row_ptr[0];
   const int64_t last = (int64_t)a.row_ptr[a.nkb] - a.row_ptr[a.nkb - 1];
-  return end >= 0 && end <= a.pick_entries && (first > last ? first : last) * rows >= 3 * end;
+  return end >= 0 && end < a.pick_entries && (first > last ? first : last) * rows >= 3 * end ? SPLIT_ALL : SPLIT_NONE;
+}
+// Whether a workgroup of 128 query rows (tile qt of head bh) has nothing to do
+// because its rows run key-split.
+__device__ __forceinline__ bool split_elsewhere(const AttnParams& a, int take, int bh, int qt) {
+  const int nqt = (a.seqlen + 255) / 256;
+  return take == SPLIT_TAIL && bh * nqt + qt / 2 >= a.batch_heads * nqt - a.n_tail;
 }
 
 // With BS (dense only) the body also writes, for every row and key block c,
@@ -156,7 +166,8 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
   // is given.
   int bh, qt;
   if constexpr (SPARSE) {
-    if (a.pick == PICK_OTHERS && pick_key_split(a)) return;
+    const int take = a.pick == PICK_OTHERS ? split_rows(a) : SPLIT_NONE;
+    if (take == SPLIT_ALL) return;
     int item = (int)blockIdx.x;
     if (item >= a.n_static) {                // the queued tail (see claim_item)
       __shared__ int s_tail;
@@ -166,6 +177,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
       if (item < 0) return;
     }
     text_first_map(item, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
+    if (split_elsewhere(a, take, bh, qt)) return;
   } else {
     int item = (int)blockIdx.x;
     if (a.claim != nullptr) {
@@ -627,7 +639,8 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
 
   int bh, pq;
   {
-    if (a.pick == PICK_OTHERS && pick_key_split(a)) return;
+    const int take = a.pick == PICK_OTHERS ? split_rows(a) : SPLIT_NONE;
+    if (take == SPLIT_ALL) return;
     int item = (int)blockIdx.x;
     if (item >= a.n_static) {                // as in attn_fwd_kernel
       __shared__ int s_tail;
@@ -637,6 +650,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
       if (item < 0) return;
     }
     text_first_map(item, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, pq);
+    if (split_elsewhere(a, take, bh, pq)) return;
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
@@ -1080,18 +1094,26 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
   __shared__ int s_redo;
 
   int bh, qt;                                              // head, 64-row tile
+  auto tail_tile = [&](int i) {      // tile i of the last n_tail 256-row items, four tiles each
+    const int nqt = (a.seqlen + 255) / 256;
+    const int item = a.batch_heads * nqt - a.n_tail + i / 4;
+    bh = item / nqt;
+    qt = (item % nqt) * 4 + i % 4;
+    return i < 4 * a.n_tail && qt < a.nqt;
+  };
   if constexpr (SPARSE) {
-    if (a.pick == PICK_SPLIT && !pick_key_split(a)) return;
-    text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
-    if (a.ends_first) qt = qt < kEndTiles ? a.nqt - kEndTiles + qt : qt - kEndTiles;
+    const int take = a.pick == PICK_SPLIT ? split_rows(a) : SPLIT_ALL;
+    if (take == SPLIT_NONE) return;
+    if (take == SPLIT_TAIL) {
+      if (!tail_tile((int)blockIdx.x)) return;
+    } else {
+      text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
+      if (a.ends_first) qt = qt < kEndTiles ? a.nqt - kEndTiles + qt : qt - kEndTiles;
+    }
   } else {
     int lid = xcd_remap((int)blockIdx.x, a.n_items);
-    if (a.n_tail > 0) {          // the last n_tail of a launch's 256-row items, four tiles each
-      const int nqt = (a.seqlen + 255) / 256;
-      const int item = a.batch_heads * nqt - a.n_tail + lid / 4;
-      bh = item / nqt;
-      qt = (item % nqt) * 4 + lid % 4;
-      if (qt >= a.nqt) return;
+    if (a.n_tail > 0) {
+      if (!tail_tile(lid)) return;
     } else {
       bh = lid / a.nqt;
       qt = lid % a.nqt;
@@ -1855,7 +1877,8 @@ static hipError_t launch_attn(const AttnParams& a, hipStream_t st) {
 template <bool SPARSE, bool BS>
 static hipError_t launch_split(AttnParams a, int D, hipStream_t st) {
   a.nqt = (a.seqlen + kSplitRows - 1) / kSplitRows;
-  a.n_items = a.n_tail > 0 ? 4 * a.n_tail : a.nqt * a.batch_heads;
+  const bool tail_only = a.n_tail > 0 && a.pick_entries == 0;    // dense; sparse that cannot be picked
+  a.n_items = tail_only ? 4 * a.n_tail : a.nqt * a.batch_heads;
   if (SPARSE) {
     const int per = a.block / kSplitRows;     // 64-row tiles per query block
     a.tq0 *= per;
@@ -1929,7 +1952,7 @@ static hipError_t plan_sparse_items(AttnParams& a, int D, hipStream_t st) {
 hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   if (a.split) return launch_split<true, false>(a, D, st);
   a.pick_entries = pick_entries(a, D);
-  if (a.pick_entries > 0) {
+  if (a.pick_entries > 0 || a.n_tail > 0) {
     a.pick = PICK_SPLIT;
     const hipError_t e = launch_split<true, false>(a, D, st);
     if (e != hipSuccess) return e;

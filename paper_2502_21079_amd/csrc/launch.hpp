@@ -8,7 +8,8 @@ namespace adaspa {
 
 typedef uint16_t u16;
 
-// Every pattern, only those that the key-split kernel is to take, only the others.
+// Every row of every pattern, only the rows that the key-split kernel is to
+// take (split_rows), only the others.
 enum { PICK_ALL = 0, PICK_SPLIT = 1, PICK_OTHERS = 2 };
 
 struct AttnParams {
@@ -32,8 +33,9 @@ struct AttnParams {
   int kb_guess, n_guess;      // sparse: first text block and the text block count (-1, 0: none),
                               // whose tiles every row begins with under the text sink
   bool split;                 // the key-split kernel takes the problem (use_key_split)
-  int n_tail;                 // dense: the last items of this launch that run key-split (split_tail)
-  int pick;                   // sparse: which patterns a launch runs (PICK_*, set by the launcher)
+  int n_tail;                 // the last 256-row items that run key-split (split_tail): dense, and
+                              // sparse patterns that keep every block
+  int pick;                   // sparse: which rows a launch runs (PICK_*, set by the launcher)
   bool ends_first;            // sparse, key-split: the tiles at both ends first (set by the launcher)
   int64_t pick_entries;       // sparse: with PICK_*, the most entries of a pattern that runs key-split
   uint32_t* claim;            // 9 work-queue counters (one per XCD + a flag), or null

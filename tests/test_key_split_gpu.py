@@ -123,8 +123,11 @@ def test_one_split_on_the_exact_path(D):
 
 # Items of 256 rows: 256 + 64 (the most that run key-split) and + 65 (none) at
 # either d, at d 64 just below the length from which they do, + 128, + 129, + 1.
-@pytest.mark.parametrize("D,heads,L", [(128, 20, 4090), (128, 107, 700), (64, 107, 700), (64, 24, 4000), (64, 77, 1200),
-                                       (128, 257, 70), (64, 10, 8192), (64, 10, 8191), (64, 3, 27301)])
+TAILS = [(128, 20, 4090), (128, 107, 700), (64, 107, 700), (64, 24, 4000), (64, 77, 1200), (128, 257, 70),
+         (64, 10, 8192), (64, 10, 8191), (64, 3, 27301)]
+
+
+@pytest.mark.parametrize("D,heads,L", TAILS)
 def test_tail_items(D, heads, L):
     """The last items of a launch that fills the chip once: every entry point
     splits the same rows (outputs equal bit for bit), whatever the groups the
@@ -154,6 +157,37 @@ def test_tail_items(D, heads, L):
         idx = torch.as_tensor(rows, device="cuda")
         check_out(out[0, h, idx], o_ref, f"h{h}")
         check_lse(lse[0, h, idx], l_ref, f"h{h}")
+
+
+@pytest.mark.parametrize("D,heads,L", TAILS)
+@pytest.mark.parametrize("block", [64, 128])
+def test_all_blocks_equal_dense_with_tail_items(D, heads, L, block):
+    """Keeping every block is dense attention bit for bit also where dense runs
+    its last items key-split: block-sparse attention splits the same rows of
+    such a pattern, with and without a text range or a workspace.  A pattern
+    that leaves out one block of one row is no such pattern."""
+    w = _w(D, L, heads=heads, block=block)
+    q, k, v = make_qkv(w, device="cuda")
+    nb = w.nblocks
+    od, ld = ad.dense_attn_lse(q, k, v)
+    rp = torch.arange(heads * nb + 1, dtype=torch.int32, device="cuda") * nb
+    ci = torch.arange(nb, dtype=torch.int32, device="cuda").repeat(heads * nb)
+    for kw in (dict(), dict(text_start=0, text_len=min(200, L)), dict(balance=False)):
+        out, lse = ad.block_sparse_attn(q, k, v, rp, ci, block=block, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(out, od) and torch.equal(lse, ld), kw
+    if nb > 1:
+        rp2 = rp.clone()
+        rp2[-1] -= 1                               # the last row without its last block
+        out, lse = ad.block_sparse_attn(q, k, v, rp2, ci, block=block)
+        torch.cuda.synchronize()
+        rows = np.arange((nb - 1) * block, L)
+        o_ref, l_ref = oracle.masked_attention(f64(q[0, -1, rows]), f64(k[0, -1]), f64(v[0, -1]),
+                                               oracle.key_mask_from_blocks(list(range(nb - 1)), L, block), w.scale)
+        check_out(out[0, -1, rows], o_ref)
+        check_lse(lse[0, -1, rows], l_ref)
+        whole = (nb - 1) * block                   # the other rows keep everything
+        check_out(out[0, :, :whole], f64(od[0, :, :whole]))
 
 
 @pytest.mark.parametrize("D,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
