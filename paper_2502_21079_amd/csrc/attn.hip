@@ -820,6 +820,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
   bf16x8 p_prev[2][2];
   bool pend = false;
   float pend_alpha = 1.f;
+  bool unset = true;                  // some row of this wave has no reference yet
   RowSums rsum;
   rsum.init(lane);
   bool bad = false;
@@ -877,7 +878,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
         if (n >= PW || (n * SPAN) / PW != slot) return;
         ld.issue_n(n, fill, rKw, rVw, kbyte, vbyte);
       };
-      first_reference(ref, s_cur, sl2, hid);
+      if (unset) unset = first_reference(ref, s_cur, sl2, hid);
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
       pipelined_step<D>(loads, sK[RS], klane, sV[RS], voff, qf, s_cur, p_prev, s_next, p_cur, o,
@@ -953,7 +954,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
         if (slot >= PW) return;
         ld.issue_dual_n(slot, fill, rKw, rVw, ka, kb, va, vb);
       };
-      first_reference<1>(ref, s_cur, sl2, hid);
+      if (unset) unset = first_reference<1>(ref, s_cur, sl2, hid);
       f32x16 s_next[2];
       bf16x8 p_cur[2][2];
       pipelined_step<D, 1>(loads, sK[RS] + half_rows, klane, sV[RS] + half_rows, voff, qf, s_cur, p_prev, s_next,
