@@ -1869,8 +1869,8 @@ __global__ __launch_bounds__(64 * kReduceWaves) void single_pass_reduce_kernel(A
 constexpr int kFewRounds = 4;
 
 template <int D, int NW, bool SPARSE>
-static hipError_t launch_attn(const AttnParams& a, hipStream_t st) {
-  hipLaunchKernelGGL((attn_fwd_kernel<D, NW, SPARSE>), dim3(a.n_wg), dim3(64 * NW), 0, st, a);
+static hipError_t launch_attn(const AttnParams& a, hipStream_t st, size_t pad = 0) {
+  hipLaunchKernelGGL((attn_fwd_kernel<D, NW, SPARSE>), dim3(a.n_wg), dim3(64 * NW), pad, st, a);
   return hipGetLastError();
 }
 
@@ -1950,6 +1950,28 @@ static hipError_t plan_sparse_items(AttnParams& a, int D, hipStream_t st) {
   return hipGetLastError();
 }
 
+// At d 64 three workgroups share a CU, but the walk of a text row, which keeps
+// every block, goes faster beside one other than beside two.  Where that walk is
+// about as long as a CU's share of all the work, a launch therefore asks for LDS
+// that leaves room for two (no result depends on it).  In steps of 64 keys the
+// walk is seqlen / 64, and the share tiles / 512 workgroups of their lists' mean
+// and about 4 more.  Two per CU are faster until the share is 1.5 times the
+// walk, by 5-9% from half the walk on in blocks of 64 and 3-6% in blocks of 128
+// (us, three and two per CU: 110,336 tokens x 2 heads at 15%, share 1.04, 1466
+// and 1373 in blocks of 64, 1387 and 1317 of 128; 16,384 x 12 at 15%, 1.08, 219
+// and 202; but 8,192 x 48 at 10%, 2.0, 3% apart the other way, 32,768 x 24 at
+// 7%, 2.0, 582 and 663, 4,096 x 48 at 15%, 1.6, 65 and 78).  A col_idx with room
+// for every block says nothing about its entries: 12% are assumed.
+static bool text_bound(const AttnParams& a) {
+  const double rows = (double)a.batch_heads * a.nkb, all = rows * a.nkb;
+  const double nnz64 = (a.col_count < all ? (double)a.col_count : 0.12 * all) * (a.block / 64);
+  const double tiles = (double)a.batch_heads * ((a.seqlen + kSplitRows - 1) / kSplitRows);
+  return a.tq1 > a.tq0 && tiles / 512 * (nnz64 / rows + 4) < 1.5 * (a.seqlen / 64);
+}
+// LDS a workgroup asks for besides its own, so that two and not three fit a CU's
+// 160 KB: the pairs of blocks of 64 hold 40 KB, the rows of blocks of 128 32 KB.
+constexpr size_t kPairPad = 20480, kRowPad = 24576;
+
 hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   if (a.split) return launch_split<true, false>(a, D, st);
   a.pick_entries = pick_entries(a, D);
@@ -1959,6 +1981,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
     if (e != hipSuccess) return e;
     a.pick = PICK_OTHERS;
   }
+  const bool two = D == 64 && text_bound(a);
   if (a.block == 64) {
     // One workgroup per pair of query blocks (128 rows); text ranges in pairs.
     a.nqt = (a.nkb + 1) / 2;
@@ -1969,7 +1992,8 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
     }
     const hipError_t e = plan_sparse_items(a, D, st);
     if (e != hipSuccess) return e;
-    if (D == 64) hipLaunchKernelGGL((attn_sparse_pair_kernel<64, 4>), dim3(a.n_wg), dim3(256), 0, st, a);
+    if (D == 64)
+      hipLaunchKernelGGL((attn_sparse_pair_kernel<64, 4>), dim3(a.n_wg), dim3(256), two ? kPairPad : 0, st, a);
     else hipLaunchKernelGGL((attn_sparse_pair_kernel<128, 4>), dim3(a.n_wg), dim3(256), 0, st, a);
     return hipGetLastError();
   }
@@ -1977,7 +2001,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   a.nqt = a.nkb;
   const hipError_t e = plan_sparse_items(a, D, st);
   if (e != hipSuccess) return e;
-  if (D == 64) return launch_attn<64, 4, true>(a, st);
+  if (D == 64) return launch_attn<64, 4, true>(a, st, two ? kRowPad : 0);
   return launch_attn<128, 4, true>(a, st);
 }
 
