@@ -75,20 +75,18 @@ constexpr int kSplitRows = 64;        // query rows per workgroup of the key-spl
 constexpr int kEndTiles = 6;
 
 // Block-sparse problems between the two ways (more tiles of 64 query rows than
-// use_key_split takes).  When the text query rows keep
-// several times the blocks of the average row, they are the critical path of
-// the kernels that walk a row in one workgroup: about `walk` us for each 64
-// keys of the sequence and 8 more.  The key-split kernel walks them four times
-// as fast, but takes its 256 workgroups at a time, each for about `tile` us
-// for every 64 keys of its row's list and `fixed` more (fitted to 8,192 to
-// 32,768 tokens, 768 to 2,048 tiles, 4 to 30% kept; at 10%, one way against
-// the other: 16,384 tokens x 4 heads 168 -> 86 us at d 64 and 226 -> 154 us at
-// d 128, 8,192 tokens x 12 heads 89 -> 80 and 121 -> 117).  The split kernel has
-// to look better by `margin` percent: it takes about 15% more than its model,
-// and the walk at d 128 about 8% more than its own, 15% in pairs of blocks of 64,
-// whose text rows share the CU with other pairs for longer (10%, d 128: 20,000
-// tokens x 8 heads 341 -> 296 us in blocks of 64 and 314 -> 292 of 128, 30,011 x
-// 6 520 -> 454 and 474 -> 440, against 15% everywhere).
+// use_key_split takes).  When the text query rows keep several times the blocks
+// of the average row, they are the critical path of the kernels that walk a row
+// in one workgroup: about `walk` for each 64 keys of the sequence.  The
+// key-split kernel walks them four times as fast, but takes its 256 workgroups
+// at a time, each for about `tile` for every 64 keys of its row's list and
+// `fixed` more.  The costs (in 1/100 us) are fitted over 3,001 to 110,336
+// tokens, 564 to 4,096 tiles, 3 to 40% kept and both block sizes (1,484
+// launches): the choice is 1.2% (d 64) and 0.9% (d 128) from the faster way on
+// average, the launch that returns at once included, and at most 11 and 13% up
+// to 25% kept.  One way and the other at 10%, blocks of 64, us: 16,384 tokens x 4
+// heads 174 and 81 at d 64, 239 and 148 at d 128; 20,000 x 8 224 and 181, 327 and
+// 290; but 16,384 x 16 198 and 238, 318 and 400.
 //
 // The two ways round differently, so the choice follows the shape and the
 // pattern alone: neither the text range that a call names nor the room in its
@@ -101,20 +99,16 @@ constexpr int kEndTiles = 6;
 constexpr int kPickMaxTiles = 4096;
 constexpr int kPickFewest = 4;  // percent of the blocks, the fewest a pattern is expected to keep
 struct PickCost {
-  int walk, tile, fixed;      // in units of 1/100 us
-  int margin;                 // percent
+  int walk, tile, fixed;
 };
-static PickCost pick_cost(int head_dim, int block) {
-  return head_dim == 64 ? PickCost{72, 29, 700, 15} : PickCost{92, 55, 800, block == 64 ? 0 : 8};
-}
-// The most entries with which the split kernel is expected to be faster by the
-// margin and more; 0 for a shape whose patterns never take it.
+// The most entries with which the split kernel is expected to be faster; 0 for a
+// shape whose patterns never take it.
 static int64_t pick_entries(const AttnParams& a, int head_dim) {
-  const PickCost c = pick_cost(head_dim, a.block);
+  const PickCost c = head_dim == 64 ? PickCost{72, 33, 700} : PickCost{92, 55, 900};
   const int64_t tiles = (int64_t)a.batch_heads * ((a.seqlen + kSplitRows - 1) / kSplitRows), nf = a.seqlen / 64;
   if (tiles > kPickMaxTiles) return 0;
   const int64_t rows = (int64_t)a.batch_heads * a.nkb;
-  const int64_t per_tile = 256 * (c.walk * nf + 800) * 100 / (tiles * (100 + c.margin)) - c.fixed;
+  const int64_t per_tile = 256 * c.walk * nf / tiles - c.fixed;
   const int64_t most = per_tile <= 0 ? 0 : per_tile * rows / (c.tile * (a.block / 64));
   return most >= rows * a.nkb / 100 * kPickFewest ? most : 0;
 }

@@ -226,8 +226,8 @@ def test_sparse_pick_by_density(D, block, kept, room):
         check_lse(lse[0, h, idx], l_ref, f"h{h}")
 
 
-# (tokens, heads, blocks of 128 kept per video row): patterns that take the
-# key split, that are too dense for it, and between the two.
+# (tokens, heads, blocks of 128 kept per video row): patterns that take the key
+# split and, the second, one that is too dense for it.
 @pytest.mark.parametrize("D,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("L,heads,kept", [(9000, 5, 3), (9000, 5, 30), (16384, 12, 6), (12001, 6, 12)])
 @pytest.mark.parametrize("text_first", [True, False])
