@@ -152,7 +152,8 @@ def _problem_ref(B, H, L, D, block, text_start, text_len, scale):
 
 
 def _problem(shape, block: int, text_start: int, text_len: int, scale: Optional[float]):
-    return _problem_ref(*map(index, (*shape, block, text_start, text_len)), 0.0 if scale is None else float(scale))
+    B, H, L, D = shape
+    return _problem_ref(*map(index, (B, H, L, D, block, text_start, text_len)), 0.0 if scale is None else float(scale))
 
 
 def _check_qkv(*ts):
@@ -197,11 +198,11 @@ def _search_args(shape, block, text_start, text_len, scale, mode, head_param_bp,
     params = tuple([int(x) for x in head_param_bp]) if head_param_bp is not None else ()
     # The library reads head_param_bp[0 .. H-1] in the per-head modes: a shorter
     # list would be read past its end.
-    shape = tuple(shape)
-    if mode != "hierarchical" and len(params) != shape[1]:
-        raise AdaspaError(f"head_param_bp needs one entry per head ({shape[1]}), got {len(params)}")
+    B, H, L, D = shape
+    if mode != "hierarchical" and len(params) != H:
+        raise AdaspaError(f"head_param_bp needs one entry per head ({H}), got {len(params)}")
     flags = (F_TEXT_SINK if text_sink else 0) | (F_SCORES_GIVEN if scores_given else 0)
-    return _search_plan(*map(index, (*shape, block, text_start, text_len)), 0.0 if scale is None else float(scale),
+    return _search_plan(*map(index, (B, H, L, D, block, text_start, text_len)), 0.0 if scale is None else float(scale),
                         _MODES[mode], flags, params, int(base_sparsity_bp), int(recall_threshold_bp))
 
 

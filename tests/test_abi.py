@@ -357,3 +357,14 @@ def test_cached_sizes_follow_values_not_objects():
     assert ad.block_search_capacity(iter((1, 2, 2048, 64)), 64, 0, 64, "topk", [2000, 2000]) == first
     with pytest.raises(TypeError):
         ad.block_search_capacity((1, 2, 2048, 64), 64.0, 0, 64, "topk", [2000, 2000])
+
+
+def test_shapes_need_four_sizes():
+    """A shape of three or five sizes is a ValueError in every size query, as
+    unpacking it was."""
+    for shape in ((1, 2, 2048), (1, 2, 2048, 64, 1)):
+        for query in (lambda: ad.dense_attn_workspace(shape), lambda: ad.block_sparse_attn_workspace(shape, 64),
+                      lambda: ad.block_search_capacity(shape, 64, 0, 64, "topk", [2000, 2000]),
+                      lambda: ad.single_pass_online_search_workspace(shape, 64, 0, 64, "hierarchical")):
+            with pytest.raises(ValueError):
+                query()
