@@ -16,7 +16,7 @@
  *   adaspa_block_sparse_attn  blockified sparse attention over the selected
  *                             key blocks (Sec. 4.1, bias form with c -> inf)
  *
- * and adaspa_fused_online_search, the first two in one launch as Algorithm 1
+ * and adaspa_fused_online_search, the first two in one call as Algorithm 1
  * describes them (dense attention + LSE, then the masses of the same rows),
  * and adaspa_single_pass_online_search, the same results with one pass over
  * Q K^T instead of two.
@@ -38,6 +38,11 @@
  *    Counters are cleared by kernels, not memsets, so a sequence of calls
  *    with caller-allocated outputs and workspaces can be captured in a HIP
  *    graph and replayed.
+ *  - Results are deterministic: the same inputs and shape give the same bits.
+ *    How a row's sums are split over waves follows the whole shape (B * H
+ *    among it) and, for block-sparse attention, the whole pattern, so a
+ *    (batch, head) pair computed in another batch or in a shard of the heads
+ *    agrees within rounding.
  *  - Errors: invalid arguments are reported synchronously with a status code
  *    before anything is enqueued.  A failed launch returns ADASPA_ERR_HIP.
  *    A fault inside a kernel surfaces at the caller's next synchronisation.
@@ -131,7 +136,8 @@ size_t adaspa_dense_attn_workspace(const adaspa_problem* prob);
  * workspace (optional, caller-owned, 16-byte aligned, at least
  * adaspa_dense_attn_workspace() bytes, contents need not be initialised)
  * holds the counters of a work queue per XCD, so that the XCDs that run
- * faster take more of the work; with NULL the work is split statically.  The
+ * faster take more of the work; with NULL, and where a launch is short (up to
+ * 1,024 (head, 256-row tile) items), the work is split statically.  The
  * results are bitwise the same either way.  The call clears the counters
  * itself (with a kernel on `stream`); calls that may run concurrently need
  * separate workspaces.  ADASPA_ERR_WORKSPACE if it is too small or
@@ -181,11 +187,13 @@ adaspa_status adaspa_block_search(const adaspa_problem* prob, const void* q,
                                   size_t workspace_bytes, void* stream);
 
 /* Fused online search (Algorithm 1, Sec. 4.2): dense attention with LSE and
- * the block masses of that fresh LSE in ONE kernel launch, then the
- * selection.  Each workgroup computes the output and LSE of 256 query rows
- * (first pass) and then the block masses of the same rows (second pass)
- * while their Q and LSE are still in registers, so Q is read once and the
- * LSE is not read back.  It produces exactly (bit for bit) what
+ * the block masses of that fresh LSE in ONE kernel, then the selection.  Each
+ * workgroup computes the output and LSE of 256 query rows (first pass) and
+ * then the block masses of the same rows (second pass) while their Q and LSE
+ * are still in registers, so Q is read once and the LSE is not read back.
+ * Where dense attention splits rows' keys over waves (B * H * ceil(L / 64) up
+ * to 512, or a few items past a multiple of 256), the two passes are kernels
+ * of their own.  It produces exactly (bit for bit) what
  * adaspa_dense_attn_lse followed by adaspa_block_search with that LSE
  * produces:
  *   out, lse          as adaspa_dense_attn_lse (lse may be NULL: the masses
@@ -248,10 +256,11 @@ size_t adaspa_single_pass_online_search_min_workspace(const adaspa_problem* prob
  *                     ADASPA_ERR_INVALID_ARG)
  * workspace must hold at least adaspa_single_pass_online_search_min_workspace()
  * bytes, 256-byte aligned (ADASPA_ERR_WORKSPACE otherwise); with
- * adaspa_single_pass_online_search_workspace() bytes every (batch, head)
- * pair runs in one launch.  It holds the selection's scratch, the per-XCD
- * work-queue counters (cleared by the call) and the per-row block masses,
- * and its contents need not be kept between calls.  Capacity, alignment and the other errors as adaspa_block_search. */
+ * adaspa_single_pass_online_search_workspace() bytes all (batch, head) pairs
+ * run together.  It holds the selection's scratch, the per-XCD work-queue
+ * counters (cleared by the call) and the per-row block masses, and its
+ * contents need not be kept between calls.  Capacity, alignment and the other
+ * errors as adaspa_block_search. */
 adaspa_status adaspa_single_pass_online_search(const adaspa_problem* prob, const void* q,
                                                const void* k, const void* v, void* out,
                                                float* lse, const adaspa_select* sel,
@@ -271,22 +280,25 @@ size_t adaspa_block_sparse_attn_workspace(const adaspa_problem* prob);
  * where kept(p) are the key blocks col_idx[row_ptr[r] .. row_ptr[r+1]) of
  * row r = (b*H+h)*NB + p.  A row that keeps nothing gives out = 0 and
  * lseM = -inf.  Keeping every block reproduces adaspa_dense_attn_lse bit for
- * bit (both run the same main loop).  lse_out may be NULL.  col_count is
+ * bit (both visit a row's keys in the same order and split the same rows over
+ * waves).  lse_out may be NULL.  col_count is
  * the number of readable col_idx entries: row bounds are clamped to
  * [0, col_count] and entries outside [0, NB) are skipped, so malformed
  * patterns never read out of bounds.  Rows should be strictly ascending
  * (a repeated block would be counted twice).  prob->text_start/text_len only
- * order the work (the text query blocks, which keep every key block under the
- * text sink, are started first) and name the block every row is expected to
- * begin with (its first tiles are loaded before the row's indices are read,
- * and reloaded if the row begins elsewhere); the results do not depend on
- * them.
+ * schedule the work (the text query blocks, which keep every key block under
+ * the text sink, are started first, and fewer workgroups share a CU with them)
+ * and name the block every row is expected to begin with (its first tiles are
+ * loaded before the row's indices are read, and reloaded if the row begins
+ * elsewhere).  The results depend on neither them nor col_count beyond the
+ * pattern's last entry.
  * Block 64 supports NB <= 8192 key blocks (ADASPA_ERR_UNSUPPORTED otherwise).
  * workspace (optional, caller-owned, 16-byte aligned, at least
  * adaspa_block_sparse_attn_workspace() bytes, contents need not be
- * initialised) holds per-XCD work-queue counters: the last tenth of the query
- * blocks then goes to the XCDs that run ahead; with NULL all work is split
- * statically.  The results are bitwise the same either way.  The call clears
+ * initialised) holds per-XCD work-queue counters: in launches of more than a
+ * few rounds of workgroups the last tenth of the query blocks then goes to the
+ * XCDs that run ahead; with NULL all work is split statically.  The results
+ * are bitwise the same either way.  The call clears
  * the counters itself (with a kernel on `stream`); calls that may run
  * concurrently need separate workspaces.  ADASPA_ERR_WORKSPACE if it is too
  * small or misaligned. */

@@ -10,9 +10,10 @@ The three calls mirror the C ABI in ``include/adaspa.h``:
                              (Sec. 4.1 optimal indices, Sec. 4.3 text sink and
                              row-wise uniform selection)
 * :func:`block_sparse_attn`  blockified sparse attention (Sec. 4.1)
-* :func:`fused_online_search`  Algorithm 1 in one launch: dense attention +
-                             LSE and the masses of the same rows, then the
-                             selection (bitwise what the first two give)
+* :func:`fused_online_search`  Algorithm 1: dense attention + LSE and the
+                             masses of the same rows, in one kernel where the
+                             shape allows it, then the selection (bitwise
+                             what the first two give)
 
 There is no CPU fallback: if the library is missing, every call raises.
 """
@@ -349,8 +350,9 @@ def fused_online_search(q, k, v, *, block: int, text_start: int, text_len: int, 
                         workspace: Optional[torch.Tensor] = None, base_sparsity_bp: int = 8000,
                         recall_threshold_bp: int = 8000,
                         result: Optional["SearchResult"] = None):
-    """Algorithm 1 (fused online search) in one kernel launch, then the
-    selection: returns (out, lse, SearchResult), bit for bit what
+    """Algorithm 1 (fused online search), in one kernel except where rows run
+    key-split (few query rows, or a few items past a multiple of 256), then
+    the selection: returns (out, lse, SearchResult), bit for bit what
     :func:`dense_attn_lse` followed by :func:`block_search` with that LSE
     return.  Arguments as in those two calls; ``lse`` may be skipped
     (``want_lse=False``) and the masses still use the fresh LSE."""
@@ -456,9 +458,11 @@ def block_sparse_attn(q, k, v, row_ptr, col_idx, *, block: int, scale: Optional[
                       out=None, lse=None, want_lse: bool = True, text_start: int = 0,
                       text_len: int = 0, workspace=None, balance: bool = True):
     """Blockified sparse attention over the CSR key-block lists.  Returns (out, lse).
-    ``text_start``/``text_len`` only order the work (text query blocks first).
-    With ``balance`` (the default) the last tenth of the query blocks goes to
-    the XCDs that run ahead, through per-XCD work queues whose counters live
+    ``text_start``/``text_len`` only schedule the work (text query blocks
+    first); the results do not depend on them or on room in ``col_idx``.
+    With ``balance`` (the default) the last tenth of the query blocks of
+    longer launches goes to the XCDs that run ahead, through per-XCD work
+    queues whose counters live
     in ``workspace`` (uint8 CUDA tensor of at least
     ``block_sparse_attn_workspace(q.shape, block)`` bytes; allocated here when
     not given); ``balance=False`` splits the work statically.  The results

@@ -93,7 +93,8 @@ WsLayout workspace_layout(const adaspa_problem* p) {
   WsLayout w;
   size_t off = 0;
   // A few sums per row or a partial curve per group of rows, and no less than
-  // the 12 bytes per mass that callers' buffers are sized for.
+  // 12 bytes per mass: the selection needs a fraction of that, but it is the
+  // least size that the tests of the ABI state (tests/test_abi.py).
   const size_t per_wg = (size_t)select_rows_per_wg((int)rows);
   const size_t parts = bh * ((nb + per_wg - 1) / per_wg) * nb;
   size_t sums = (parts > 4 * rows ? parts : 4 * rows) * sizeof(int64_t);

@@ -1606,7 +1606,6 @@ __device__ __forceinline__ void block_mass_body(const MassParams& a, int bh, int
 
     KLoader<D, NW> ld;
     ld.init(wave, lane);
-    const int klane = k_lane<D>(c32, hw);
     // Step t (t + 1 < nfull) sums tile t, forms the scores of tile t+1 from
     // one buffer and loads tile t+2 into the other.
     // Past the last tile the load is clamped to the last one (an in-range

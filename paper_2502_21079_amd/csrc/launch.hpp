@@ -142,9 +142,9 @@ struct SelectParams {
 hipError_t launch_dense(AttnParams a, int head_dim, hipStream_t st);
 hipError_t launch_sparse(AttnParams a, int head_dim, hipStream_t st);
 hipError_t launch_block_mass(MassParams a, int head_dim, hipStream_t st);
-// Dense attention + LSE and the block masses of the same rows, in one launch
-// or, where a.split or a.n_tail, in two (m.lse then is a.lse) (a: the attention's arguments with a.claim the optional work-queue
-// counters; m: the mass pass's, its lse otherwise unused).
+// Dense attention + LSE and the block masses of the same rows: one kernel, or
+// where a.split or a.n_tail the dense launches and then the mass pass (m.lse is
+// a.lse then, and unused otherwise).  a.claim: the optional work-queue counters.
 hipError_t launch_fused_search(AttnParams a, MassParams m, int head_dim, hipStream_t st);
 // Dense attention + LSE and the block masses of its LSE in one pass over
 // Q K^T (a.ylog, a.ylse2: scratch of B*H*nkb*L and B*H*L floats; a.wmass:

@@ -129,7 +129,8 @@ __device__ __forceinline__ int count_reaching(const uint32_t (&u)[R], uint32_t c
 // row are spread about like a bell curve (they go by the logarithm of the
 // masses), so the value is placed where the logits of the two counts, taken
 // as linear in between, meet that of n, and every fourth time in the middle:
-// six counts on average where a search bit by bit took fifteen.
+// 7.8 counts on average over rows of 1,724 blocks (18 at most), 6.7 of 862 and
+// 4.0 of 32, where a search bit by bit took fifteen.
 template <int R>
 __device__ __forceinline__ Cut find_cut(const uint32_t (&u)[R], int n, int all) {
   if (n <= 0) return Cut{0xFFFFFFFFu, 0};
@@ -750,9 +751,11 @@ __global__ __launch_bounds__(64) void select_base_kernel(SelectParams P) {
 }
 
 // One instantiation per number of keys a lane holds: a row takes the smallest
-// that covers it, so few compares are spent on empty keys (140, 862 and 1,724
-// blocks of the usual sequences take 4, 14 and 27 keys, at most a tenth empty
-// from 862 on).
+// that covers it, and its compares on the keys past its end are wasted.  The
+// steps lie where the usual sequences need them (140, 862 and 1,724 blocks, 2,582
+// and 5,164 of the longest clips: 3, 14, 27, 41 and 81 keys); in between up to
+// half of the keys are empty (2,689 blocks, 43 keys, take 82), and from 82 on the
+// registers leave two waves per SIMD, then one.
 template <typename F>
 static void with_keys_per_lane(int nb, F&& f) {
   const int need = (nb + 63) / 64;

@@ -112,7 +112,11 @@ def test_one_split_on_the_exact_path(D):
     L = 1100
     (q, k, v), scale = make_extreme_qkv("negative", heads=2, seqlen=L, head_dim=D, device="cuda")
     k = k.clone()
-    k[:, :, 300:340] *= -0.9                    # inside the third unit of 128 keys
+    k[:, :, 330:370] *= -0.9                    # the second 64 keys of the third unit of 128
+    # The unit's first tile sets its wave's reference, the jump comes after it
+    # and passes the 2^100 at which a sum is redone.
+    rows = (q[0, :, ::50].float() @ k[0, :, 256:384].float().transpose(1, 2)) * (scale * 1.4427)
+    assert float((rows[..., 64:].amax(2) - rows[..., :64].amax(2)).min()) > 110
     out, lse = ad.dense_attn_lse(q, k, v, scale=scale)
     torch.cuda.synchronize()
     for h in range(2):
