@@ -95,7 +95,7 @@ WsLayout workspace_layout(const adaspa_problem* p) {
   // A few sums per row or a partial curve per group of rows, and no less than
   // 12 bytes per mass: the selection needs a fraction of that, but it is the
   // least size that the tests of the ABI state (tests/test_abi.py).
-  const size_t per_wg = (size_t)select_rows_per_wg((int)rows);
+  const size_t per_wg = (size_t)select_rows_per_wg((int)rows, (int)nb);
   const size_t parts = bh * ((nb + per_wg - 1) / per_wg) * nb;
   size_t sums = (parts > 4 * rows ? parts : 4 * rows) * sizeof(int64_t);
   sums = sums > 12 * rows * nb ? sums : 12 * rows * nb;

@@ -105,11 +105,16 @@ struct MassParams {
 constexpr int kMaxHeads = 512;
 constexpr int kMaxBlocks = 8192;
 
-// Rows whose masses one workgroup of the coverage curve adds up (four waves,
-// each one to sixteen rows): few enough for four workgroups per CU, and at
-// most 64, so that the partial curves each head's workgroup then adds up stay
-// few.
-inline int select_rows_per_wg(int rows) {
+// Rows whose masses one workgroup of the coverage curve adds up.  Up to
+// kWaveBlocks blocks a wave sorts a row: four waves, each one to sixteen rows,
+// few enough for four workgroups per CU, and at most 64, so that the partial
+// curves to be added up stay few.  Longer rows are sorted by the whole workgroup
+// one after another, so one or two each (one row of curves per row of masses,
+// 2,582 blocks x 1 head 399 us, with two 464, with four 481; x 12 heads 3677,
+// 3535 and 5703).
+constexpr int kWaveBlocks = 2048;
+inline int select_rows_per_wg(int rows, int nb) {
+  if (nb > kWaveBlocks) return rows >= 8192 ? 2 : 1;
   const int per_wave = rows / 4096;
   return 4 * (per_wave < 1 ? 1 : (per_wave > 16 ? 16 : per_wave));
 }
@@ -126,7 +131,9 @@ struct SelectParams {
   int32_t* ws_headk;          // [B*H]
   int32_t* ws_base;           // [B*H] first col_idx entry of each head (many heads only)
   int rows_per_wg, n_parts;   // COVERAGE: rows of one partial curve; parts per head (also HIERARCHICAL)
-  int base_ready;             // ws_base holds the heads' first entries (both set by the launcher)
+  int base_ready;             // ws_base holds the heads' first entries
+  int summed;                 // COVERAGE: the first partial curve of a head holds the sum of all
+                              // (rows_per_wg to summed are set by the launcher)
   int batch_heads;
   int heads;
   int nb;

@@ -642,6 +642,29 @@ __global__ __launch_bounds__(SEL_NT) void select_recall_kernel(SelectParams P) {
   }
 }
 
+// COVERAGE: the partial curves of each head added up over 64 positions per
+// workgroup, into the first of them (its positions are read by the workgroup
+// that writes them, before it does).
+constexpr int kSumPositions = 64;
+__global__ __launch_bounds__(SEL_NT) void select_curve_sum_kernel(SelectParams P) {
+  __shared__ int64_t part[SEL_WAVES][kSumPositions];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * kSumPositions + lane, nb = P.nb;
+  int64_t* s = P.ws_sums + (size_t)blockIdx.y * P.n_parts * nb;
+  int64_t v = 0;
+  if (i < nb) {
+#pragma unroll 8
+    for (int c = wave; c < P.n_parts; c += SEL_WAVES) v += s[(size_t)c * nb + i];
+  }
+  part[wave][lane] = v;
+  __syncthreads();
+  if (wave == 0 && i < nb) {
+#pragma unroll
+    for (int j = 1; j < SEL_WAVES; ++j) v += part[j][lane];
+    s[i] = v;
+  }
+}
+
 // COVERAGE: the head's curve from the partial curves, and the smallest count
 // whose kept share reaches the target (one workgroup per head).
 constexpr int SEL_HEAD_NT = 1024;
@@ -649,6 +672,7 @@ __global__ __launch_bounds__(SEL_HEAD_NT) void select_coverage_kernel(SelectPara
   __shared__ unsigned long long cv[kMaxBlocks];
   const int bh = blockIdx.x, nb = P.nb;
   const int64_t* s = P.ws_sums + (size_t)bh * P.n_parts * nb;
+  const int n_parts = P.summed ? 1 : P.n_parts;
   // Where a head has fewer positions than threads, the partial curves are
   // dealt out over the spare ones.
   const int cols = (nb + 63) / 64 * 64, groups = cols < SEL_HEAD_NT ? SEL_HEAD_NT / cols : 1;
@@ -659,7 +683,7 @@ __global__ __launch_bounds__(SEL_HEAD_NT) void select_coverage_kernel(SelectPara
     for (int i = (int)threadIdx.x - g * cols; i < nb; i += SEL_HEAD_NT) {
       int64_t v = 0;
 #pragma unroll 8
-      for (int c = g; c < P.n_parts; c += groups) v += s[(size_t)c * nb + i];
+      for (int c = g; c < n_parts; c += groups) v += s[(size_t)c * nb + i];
       atomicAdd(&cv[i], (unsigned long long)v);
     }
   __syncthreads();
@@ -771,6 +795,14 @@ static void with_keys_per_lane(int nb, F&& f) {
   else f(std::integral_constant<int, 128>{});
 }
 
+// Entries of a head's partial curves from which they are added up by a launch of
+// their own, over the whole chip, instead of by the one workgroup that looks for
+// the head's count (a whole selection, us, without and with that launch: 24,727
+// entries, 313 blocks x 2 heads, 25.4 and 26.1; 31,500, 500 x 24, 68.1 and 67.3;
+// 62,500, 500 x 3, 33.5 and 30.0; 743,000, 1,724 x 3, 235 and 154; 1.05 million,
+// 2,049 x 1, 566 and 445).
+constexpr int64_t kSumEntries = 30000;
+
 hipError_t launch_select(SelectParams P, hipStream_t st) {
   const int rows = P.batch_heads * P.nb;
   const dim3 per_row((rows + SEL_WAVES - 1) / SEL_WAVES), nt(SEL_NT);
@@ -783,7 +815,7 @@ hipError_t launch_select(SelectParams P, hipStream_t st) {
     return hipGetLastError();
   }
   if (P.mode == 1) {
-    P.rows_per_wg = select_rows_per_wg(rows);
+    P.rows_per_wg = select_rows_per_wg(rows, P.nb);
     P.n_parts = (P.nb + P.rows_per_wg - 1) / P.rows_per_wg;
     const dim3 grid(P.n_parts, P.batch_heads);
     const int need = (P.nb + 63) / 64;
@@ -795,6 +827,10 @@ hipError_t launch_select(SelectParams P, hipStream_t st) {
     else if (need <= 32) hipLaunchKernelGGL((select_curve_kernel<32>), grid, nt, 0, st, P);
     else if (need <= 64) hipLaunchKernelGGL((select_curve_long_kernel<16>), grid, nt, 0, st, P);
     else hipLaunchKernelGGL((select_curve_long_kernel<32>), grid, nt, 0, st, P);
+    P.summed = (int64_t)P.n_parts * P.nb >= kSumEntries;
+    if (P.summed)
+      hipLaunchKernelGGL(select_curve_sum_kernel, dim3((P.nb + kSumPositions - 1) / kSumPositions, P.batch_heads), nt,
+                         0, st, P);
     hipLaunchKernelGGL(select_coverage_kernel, dim3(P.batch_heads), dim3(SEL_HEAD_NT), 0, st, P);
   } else {
     P.n_parts = (P.nb + SEL_WAVES - 1) / SEL_WAVES;

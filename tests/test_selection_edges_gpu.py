@@ -1,7 +1,8 @@
 """Block selection at the sizes where its kernels change: one key per lane and
 one more, every step of the keys a lane holds, the longest row sorted in a
-wave's registers and the shortest one sorted in LDS, rows of one block, and
-more heads than a row's wave adds up by itself.  Masses hold ties and every
+wave's registers and the shortest one sorted in LDS, rows of one block, partial
+curves added up by a launch of their own and by the head's workgroup, and more
+heads than a row's wave adds up by itself.  Masses hold ties and every
 special value (NaN, infinities, zeros of both signs, negatives, subnormals,
 masses past the exact sums' cap, halves of the last kept bit).  Everything is
 bit-exact against the oracle on the same scores."""
@@ -65,3 +66,9 @@ def test_selection_at_the_kernels_edges(case, mode):
 @pytest.mark.parametrize("nb,mode", LONG)
 def test_selection_of_long_rows(nb, mode):
     _check(nb, 1, 1, 0, 4, mode)
+
+
+def test_two_long_rows_per_workgroup():
+    """Four heads of 2,049 rows are the fewest long rows of which a workgroup of
+    the coverage curve takes two (the last one of a head has a single row)."""
+    _check(2049, 1, 4, 0, 4, "coverage")
