@@ -1071,8 +1071,9 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
 // Which wave takes a tile depends only on the tile's place in the row's list
 // (dense: all tiles), so a row that keeps every block gives bit for bit the
 // dense result here too.  2,048 tokens x 2 heads, d 64: dense 33 -> 14 us,
-// block-sparse (20%, block 64) 29 -> 15 us; a step takes about 1.1 us, of which
-// the four tiles' loads are half and their latency most of the rest.
+// block-sparse (20%, block 64) 29 -> 15 us; a step takes about 1.1 us, the
+// matrix pipe of the 64 CUs in use is busy a fifth of the time and the waves
+// wait 38% of theirs for loads and barriers.
 // ---------------------------------------------------------------------------
 template <int D, bool SPARSE, bool BS>
 __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
