@@ -67,12 +67,19 @@ struct NoTail {
 
 constexpr int kSplits = 4;            // waves that share a row's keys
 constexpr int kSplitRows = 64;        // query rows per workgroup of the key-split kernel
-// Where a call names no text range, a picked pattern starts these many tiles at
-// both ends of the sequence first (256 tokens of text overlap up to three blocks
-// of 128), as it does the text rows otherwise (10%, us, without and with it:
-// 4,096 tokens x 16 heads 70 -> 45 at d 64 and 116 -> 73 at d 128, 16,384 x 6
-// 160 -> 108 and 278 -> 178).
-constexpr int kEndTiles = 6;
+// Where a block-sparse call names no text range, its text rows, the longest,
+// are still most likely at one end of the sequence: the tiles of these many rows
+// at both ends are started first, as the named text rows are otherwise (256 tokens
+// of text overlap up to three blocks of 128).  10%, text last, us, without and with
+// it: 3,003 tokens x 24 heads at d 128 111 -> 56 in blocks of 64 and 109 -> 55 of
+// 128, 20,000 x 12 at d 64 459 -> 254 and 421 -> 239; key-split, 4,096 x 16, 70 ->
+// 45 at d 64 and 116 -> 73 at d 128.  Patterns without text rows gain nothing:
+// blocks of 128 pay nothing either (16,384 x 12, 10%, d 64 89.4 -> 89.2), pairs up
+// to 5% at d 64 (113 -> 119).  At d 128 pairs pay 3-6% past two rounds of workgroups
+// (16,384 x 12 228 -> 240, 32,768 x 8 493 -> 525; 9,001 x 12 92.1 -> 92.5), so there
+// the order stays the sequence's.
+constexpr int kEndRows = 384;
+constexpr int kEndPairs = 1024;       // the most pairs at d 128: two rounds
 
 // Block-sparse problems between the two ways (more tiles of 64 query rows than
 // use_key_split takes).  When the text query rows keep several times the blocks
@@ -111,6 +118,17 @@ static int64_t pick_entries(const AttnParams& a, int head_dim) {
   const int64_t per_tile = 256 * c.walk * nf / tiles - c.fixed;
   const int64_t most = per_tile <= 0 ? 0 : per_tile * rows / (c.tile * (a.block / 64));
   return most >= rows * a.nkb / 100 * kPickFewest ? most : 0;
+}
+// The tile that stands at place qt of the order in which the ends come first.
+__device__ __forceinline__ int from_ends(const AttnParams& a, int qt) {
+  return a.ends == 0 ? qt : (qt < a.ends ? a.nqt - a.ends + qt : qt - a.ends);
+}
+static void ends_first(AttnParams& a, int tile_rows) {
+  a.ends = a.tq1 > a.tq0 || a.nqt * tile_rows <= 2 * kEndRows ? 0 : kEndRows / tile_rows;
+  if (a.ends > 0) {
+    a.tq0 = 0;
+    a.tq1 = 2 * a.ends;
+  }
 }
 // Which rows of a pattern run key-split: the same answer in every workgroup of
 // both kernels.  A pattern that keeps every block splits the rows that dense
@@ -171,6 +189,7 @@ __device__ __forceinline__ void attn_fwd_body(AttnParams a, Tail&& tail) {
       if (item < 0) return;
     }
     text_first_map(item, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
+    qt = from_ends(a, qt);
     if (split_elsewhere(a, take, bh, qt)) return;
   } else {
     int item = (int)blockIdx.x;
@@ -644,6 +663,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 1 : kWavesPerSimd<D>) void attn_
       if (item < 0) return;
     }
     text_first_map(item, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, pq);
+    pq = from_ends(a, pq);
     if (split_elsewhere(a, take, bh, pq)) return;
   }
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1104,7 +1124,7 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(AttnParams a) {
       if (!tail_tile((int)blockIdx.x)) return;
     } else {
       text_first_map((int)blockIdx.x, a.n_items, a.nqt, a.tq0, a.tq1 - a.tq0, bh, qt);
-      if (a.ends_first) qt = qt < kEndTiles ? a.nqt - kEndTiles + qt : qt - kEndTiles;
+      qt = from_ends(a, qt);
     }
   } else {
     int lid = xcd_remap((int)blockIdx.x, a.n_items);
@@ -1879,8 +1899,7 @@ static hipError_t launch_split(AttnParams a, int D, hipStream_t st) {
     a.tq0 *= per;
     a.tq1 = a.tq1 * per < a.nqt ? a.tq1 * per : a.nqt;
     if (a.tq1 - a.tq0 >= a.nqt) a.tq0 = a.tq1 = 0;
-    a.ends_first = a.pick == PICK_SPLIT && a.tq1 == 0 && a.nqt > 2 * kEndTiles;
-    if (a.ends_first) a.tq1 = 2 * kEndTiles;
+    if (a.pick == PICK_SPLIT) ends_first(a, kSplitRows);
   }
   if (D == 64) hipLaunchKernelGGL((attn_split_kernel<64, SPARSE, BS>), dim3(a.n_items), dim3(512), 0, st, a);
   else hipLaunchKernelGGL((attn_split_kernel<128, SPARSE, BS>), dim3(a.n_items), dim3(512), 0, st, a);
@@ -1976,7 +1995,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
     if (e != hipSuccess) return e;
     a.pick = PICK_OTHERS;
   }
-  const bool two = D == 64 && text_bound(a);
+  const bool two = D == 64 && text_bound(a);      // by the range that the call names
   if (a.block == 64) {
     // One workgroup per pair of query blocks (128 rows); text ranges in pairs.
     a.nqt = (a.nkb + 1) / 2;
@@ -1985,6 +2004,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
       a.tq1 = (a.tq1 + 1) / 2;
       if (a.tq1 - a.tq0 >= a.nqt) a.tq0 = a.tq1 = 0;
     }
+    if (D == 64 || a.nqt * a.batch_heads <= kEndPairs) ends_first(a, 128);
     const hipError_t e = plan_sparse_items(a, D, st);
     if (e != hipSuccess) return e;
     if (D == 64)
@@ -1994,6 +2014,7 @@ hipError_t launch_sparse(AttnParams a, int D, hipStream_t st) {
   }
   // One workgroup per query block of 128 (four waves).
   a.nqt = a.nkb;
+  ends_first(a, 128);
   const hipError_t e = plan_sparse_items(a, D, st);
   if (e != hipSuccess) return e;
   if (D == 64) return launch_attn<64, 4, true>(a, st, two ? kRowPad : 0);

@@ -36,7 +36,8 @@ struct AttnParams {
   int n_tail;                 // the last 256-row items that run key-split (split_tail): dense, and
                               // sparse patterns that keep every block
   int pick;                   // sparse: which rows a launch runs (PICK_*, set by the launcher)
-  bool ends_first;            // sparse, key-split: the tiles at both ends first (set by the launcher)
+  int ends;                   // sparse: tiles at each end of the sequence that come first when the
+                              // call names no text range (set by the launcher)
   int64_t pick_entries;       // sparse: with PICK_*, the most entries of a pattern that runs key-split
   uint32_t* claim;            // 9 work-queue counters (one per XCD + a flag), or null
   int n_items;                // work items: (head, query tile) or (head, query block / pair)

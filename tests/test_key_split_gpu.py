@@ -257,3 +257,22 @@ def test_sparse_results_follow_the_pattern_alone(D, block, L, heads, kept, text_
             base = base or res
             torch.cuda.synchronize()
             assert torch.equal(res[0], base[0]) and torch.equal(res[1], base[1]), (cols.numel(), start, n_text)
+
+
+# Without a text range the tiles of 384 rows at both ends come first, from the
+# first length with rows between them (769); in blocks of 64 at d 128 up to 1,024
+# pairs (128 heads of 8).  The last case has a work queue.
+@pytest.mark.parametrize("D,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("L,heads", [(768, 48), (769, 48), (900, 43), (1000, 128), (1000, 129), (1025, 300)])
+def test_order_without_a_text_range_covers_every_row(D, block, L, heads):
+    """Calls with and without a text range run the same rows."""
+    w = _w(D, L, heads=heads, block=block, text=100)
+    q, k, v = make_qkv(w, device="cuda")
+    nb = w.nblocks
+    g = np.random.default_rng(L)
+    lists = [sorted(g.choice(nb, min(nb, 4), replace=False).tolist()) for _ in range(heads * nb)]
+    rp, ci = _csr(lists)
+    named = ad.block_sparse_attn(q, k, v, rp, ci, block=block, text_start=0, text_len=100)
+    plain = ad.block_sparse_attn(q, k, v, rp, ci, block=block)
+    torch.cuda.synchronize()
+    assert torch.equal(named[0], plain[0]) and torch.equal(named[1], plain[1])
